@@ -481,8 +481,11 @@ __device__ __forceinline__ uint32_t elem_off(int p, int q, int rows, int ld, int
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const void *base, uint64_t bytes)
 {
+    // The 64-bit comparison runs on the vector unit; without the readfirstlane the compiler
+    // takes the descriptor for divergent and wraps each load in a loop over its values.
     const uint32_t n = bytes < OOR_OFFSET ? (uint32_t)bytes : OOR_OFFSET;
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)n, 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0,
+                                             __builtin_amdgcn_readfirstlane((int)n), 0x00020000);
 }
 
 template <int BP, int BQ, int MK, int E, int AH = 0>
@@ -800,46 +803,77 @@ struct EpiI8Row {
 // slot (t+1)%4 for the next step, so that no slot is read while another workgroup writes it.
 struct Fp8 {
     static __device__ __forceinline__ float scale_of(float amax) { return amax > 0.0f ? amax / 448.0f : 1.0f; }
-    static __device__ __forceinline__ float clamp(float x) { return fminf(fmaxf(x, -448.0f), 448.0f); }
-    // value of byte e of 8 packed codes
-    static __device__ __forceinline__ float decode(const u32x2_t &c, int e)
+    // values of the eight packed codes
+    static __device__ __forceinline__ void decode8(const u32x2_t &c, float (&x)[8])
     {
-        const int w = (int)c[e >> 2];
-        switch (e & 3) {
-        case 0: return __builtin_amdgcn_cvt_f32_fp8(w, 0);
-        case 1: return __builtin_amdgcn_cvt_f32_fp8(w, 1);
-        case 2: return __builtin_amdgcn_cvt_f32_fp8(w, 2);
-        default: return __builtin_amdgcn_cvt_f32_fp8(w, 3);
-        }
-    }
-    // 8 values (already scaled) -> 8 codes
-    static __device__ __forceinline__ u32x2_t encode8(const float (&x)[8])
-    {
-        u32x2_t c;
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            const int lo = __builtin_amdgcn_cvt_pk_fp8_f32(clamp(x[4 * k]), clamp(x[4 * k + 1]), 0, false);
-            c[k] = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(clamp(x[4 * k + 2]), clamp(x[4 * k + 3]), lo, true);
+            const f32x2_t lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)c[k], false);
+            const f32x2_t hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)c[k], true);
+            x[4 * k] = lo[0];
+            x[4 * k + 1] = lo[1];
+            x[4 * k + 2] = hi[0];
+            x[4 * k + 3] = hi[1];
+        }
+    }
+    // 8 values (already scaled) -> 8 codes, clamped to [lo, 448].  The median gives -448 for a
+    // NaN with lo = -448, like a maximum and a minimum in turn.
+    static __device__ __forceinline__ u32x2_t encode8(const float (&x)[8], const float (&lo)[8])
+    {
+        u32x2_t c;
+        float y[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) y[e] = __builtin_amdgcn_fmed3f(x[e], lo[e], 448.0f);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int h = __builtin_amdgcn_cvt_pk_fp8_f32(y[4 * k], y[4 * k + 1], 0, false);
+            c[k] = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(y[4 * k + 2], y[4 * k + 3], h, true);
         }
         return c;
     }
-    // Record a wave's amax into the slot (one atomic per wave, skipped when the slot already
-    // holds at least as much; amax >= 0, so its bit pattern orders like the value).
-    static __device__ __forceinline__ void record(float *ring, int slot, float amax, int lane)
+    static __device__ __forceinline__ u32x2_t encode8(const float (&x)[8])
     {
-#pragma unroll
-        for (int d = 32; d > 0; d >>= 1) amax = fmaxf(amax, __shfl_xor(amax, d));
-        if (lane == 0) {
-            unsigned *p = reinterpret_cast<unsigned *>(ring + slot);
-            const unsigned bits = __float_as_uint(amax);
-            if (bits > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(p, bits);
-        }
+        const float lo[8] = {-448.0f, -448.0f, -448.0f, -448.0f, -448.0f, -448.0f, -448.0f, -448.0f};
+        return encode8(x, lo);
+    }
+    // A wave's maximum of amax >= 0 into its place of the workgroup's: on the bit pattern,
+    // which orders like the value, by lane exchanges without LDS round trips.
+    static __device__ __forceinline__ void put_max(int *dst, int wave, float amax, int lane)
+    {
+        int b = __float_as_int(amax);
+        b = max(b, dpp_i<0xB1>(b));
+        b = max(b, dpp_i<0x4E>(b));
+        b = max(b, dpp_i<0x141>(b));
+        b = max(b, dpp_i<0x128>(b));
+        const auto h = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+        b = max((int)h[0], (int)h[1]);
+        const auto w = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+        b = max((int)w[0], (int)w[1]);
+        if (lane == 0) dst[wave] = b;
+    }
+    // Record the maximum of four waves into the slot: one atomic per workgroup, skipped when
+    // the slot already holds at least as much.  The slots of a tensor are one address for the
+    // whole launch, so reads and atomics of it queue up: one of each per
+    // wave held the end of every tile back (fp8 weights and moments at 4096 x 4096, T = 512: 48
+    // against 42 us per launch; atomics alone, without the read first, 55 us).
+    static __device__ __forceinline__ void record(float *ring, int slot, const int *amax)
+    {
+        const unsigned b = (unsigned)max(max(amax[0], amax[1]), max(amax[2], amax[3]));
+        unsigned *p = reinterpret_cast<unsigned *>(ring + slot);
+        if (b > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(p, b);
     }
 };
 
 // AdamW with fp8 weights (WF8) and / or fp8 moments (MF8; m and sqrt(v) stored, the sqrt(v)
 // codes at least the smallest positive code when v' > 0); the other tensors bf16.  The
 // update reads the decoded state and runs in fp32 as everywhere else.
+//
+// Bound by the stream waves' instructions: with few bytes per element the epilogue (10.6 of a
+// tile's 20.9 us at T = 512) and the token loop run one after the other in a workgroup.
+// Branch-free buffer loads, codes converted in pairs, scales folded into the recurrence's
+// constants, one median per clamp and maxima recorded once per workgroup take the fp8
+// weight + moment step on 14336 x 4096 at T = 512 from 136 to 126 us, on 4096 x 4096 from
+// 45.2 to 39.8 us (fp8 moments 140 to 137 us and, on 4096 x 14336, 147 to 137 us).
 template <int BP, int BQ, bool WF8, bool MF8>
 struct EpiQ {
     using M = EpiMap<BP, BQ>;
@@ -852,31 +886,33 @@ struct EpiQ {
     template <int I>
     __device__ __forceinline__ void prefetch_pass(const Args &a, int p0, int q0, int s)
     {
+        // buffer loads: elements outside the matrix read as zero
         const int rs = s / M::LPR, q = q0 + (s % M::LPR) * 8;
         const int p = p0 + I * M::RPP + rs;
-        const u32x4_t z4 = {0u, 0u, 0u, 0u};
-        const u32x2_t z2 = {0u, 0u};
-        if constexpr (WF8) pw8[I] = z2; else pw16[I] = z4;
-        if constexpr (MF8) { pm8[I] = z2; pv8[I] = z2; } else { pm16[I] = z4; pv16[I] = z4; }
-        if (q < a.d_in && p < a.d_out) {
-            const size_t off = (size_t)p * a.d_in + q;
-            if constexpr (WF8) pw8[I] = ld_nt<u32x2_t>(reinterpret_cast<const uint8_t *>(a.W) + off);
-            else pw16[I] = ld_nt<u32x4_t>(a.W + off);
-            if constexpr (MF8) {
-                pm8[I] = ld_nt<u32x2_t>(static_cast<const uint8_t *>(a.m) + off);
-                pv8[I] = ld_nt<u32x2_t>(static_cast<const uint8_t *>(a.v) + off);
-            } else {
-                pm16[I] = ld_nt<u32x4_t>(static_cast<const uint16_t *>(a.m) + off);
-                pv16[I] = ld_nt<u32x4_t>(static_cast<const uint16_t *>(a.v) + off);
-            }
+        const uint64_t n = (uint64_t)a.d_out * (uint64_t)a.d_in;
+        const uint32_t off = elem_off(p, q, a.d_out, a.d_in, 1);
+        const uint32_t off2 = off == OOR_OFFSET ? off : 2u * off;
+        if constexpr (WF8) pw8[I] = __builtin_amdgcn_raw_buffer_load_b64(rsrc_of(a.W, n), off, 0, 2);
+        else pw16[I] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_of(a.W, 2ull * n), off2, 0, 2);
+        if constexpr (MF8) {
+            pm8[I] = __builtin_amdgcn_raw_buffer_load_b64(rsrc_of(a.m, n), off, 0, 2);
+            pv8[I] = __builtin_amdgcn_raw_buffer_load_b64(rsrc_of(a.v, n), off, 0, 2);
+        } else {
+            pm16[I] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_of(a.m, 2ull * n), off2, 0, 2);
+            pv16[I] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_of(a.v, 2ull * n), off2, 0, 2);
         }
     }
 
     template <int I = 0>
-    __device__ __forceinline__ void prefetch(const Args &a, int p0, int q0, int s)
+    __device__ __forceinline__ void prefetch_rows(const Args &a, int p0, int q0, int s)
     {
         prefetch_pass<I>(a, p0, q0, s);
-        if constexpr (I + 1 < M::NPASS) prefetch<I + 1>(a, p0, q0, s);
+        if constexpr (I + 1 < M::NPASS) prefetch_rows<I + 1>(a, p0, q0, s);
+    }
+
+    __device__ __forceinline__ void prefetch(const Args &a, int p0, int q0, int s)
+    {
+        prefetch_rows(a, p0, q0, s);
     }
 
     static __device__ __forceinline__ float bf(const u32x4_t &u, int e)
@@ -884,7 +920,8 @@ struct EpiQ {
         return (e & 1) ? bf_hi(u[e >> 1]) : bf_lo(u[e >> 1]);
     }
 
-    __device__ __forceinline__ void run(const Args &a, int p0, int q0, int s, const float *Gs)
+    // Contains one barrier, which the math waves also execute.
+    __device__ __forceinline__ void run(const Args &a, int p0, int q0, int s, const float *Gs, int *amax)
     {
         const int rs = s / M::LPR, qo = (s % M::LPR) * 8, q = q0 + qo;
         const Hyper h = a.h;
@@ -900,6 +937,11 @@ struct EpiQ {
             v_dec = Fp8::scale_of(a.vs[dec]);
             v_inv = 1.0f / Fp8::scale_of(a.vs[enc]);
         }
+        // A decode scale multiplies its code by way of the recurrence's constant: m' = (b1 s)
+        // q + c1 g, v' = (b2 s^2) q^2 + c2 g^2 (q^2 is exact), W' = (wdf s) q - update.
+        const float kw = WF8 ? h.wdf * w_dec : h.wdf;
+        const float km = MF8 ? h.b1 * m_dec : h.b1;
+        const float kv = MF8 ? h.b2 * v_dec * v_dec : h.b2;
         float aw = 0.0f, am = 0.0f, av = 0.0f;
 #pragma unroll
         for (int i = 0; i < M::NPASS; ++i) {
@@ -908,72 +950,95 @@ struct EpiQ {
             const float *gr = Gs + (i * M::RPP + rs) * M::GP + qo;
             const f32x4_t g0 = *reinterpret_cast<const f32x4_t *>(gr);
             const f32x4_t g1 = *reinterpret_cast<const f32x4_t *>(gr + 4);
-            float wo[8], mo[8], vo[8], ro[8];
+            float w0[8], m0[8], v0[8], wo[8], mo[8], vo[8], ro[8];
+            if constexpr (WF8) Fp8::decode8(pw8[i], w0);
+            if constexpr (MF8) {
+                Fp8::decode8(pm8[i], m0);
+                Fp8::decode8(pv8[i], v0);
+            }
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const float g = e < 4 ? g0[e] : g1[e - 4];
-                const float w = WF8 ? w_dec * Fp8::decode(pw8[i], e) : bf(pw16[i], e);
-                float m0, v0;
+                if constexpr (!WF8) w0[e] = bf(pw16[i], e);
                 if constexpr (MF8) {
-                    m0 = m_dec * Fp8::decode(pm8[i], e);
-                    const float r0 = v_dec * Fp8::decode(pv8[i], e);
-                    v0 = r0 * r0;
+                    v0[e] *= v0[e];
                 } else {
-                    m0 = bf(pm16[i], e);
-                    v0 = bf(pv16[i], e);
+                    m0[e] = bf(pm16[i], e);
+                    v0[e] = bf(pv16[i], e);
                 }
-                adamw_elem(g, w, m0, v0, h, wo[e], mo[e], vo[e], ro[e]);
-            }
-            if (ok) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    aw = fmaxf(aw, fabsf(wo[e]));
+                Hyper hk = h;
+                hk.b1 = km;
+                hk.b2 = kv;
+                hk.wdf = kw;
+                adamw_elem(g, w0[e], m0[e], v0[e], hk, wo[e], mo[e], vo[e], ro[e]);
+                // elements outside the matrix are zero here and leave the maxima alone
+                if constexpr (WF8) aw = fmaxf(aw, fabsf(wo[e]));
+                if constexpr (MF8) {
                     am = fmaxf(am, fabsf(mo[e]));
                     av = fmaxf(av, ro[e]);
                 }
-                const size_t off = (size_t)p * a.d_in + q;
-                if constexpr (WF8) {
-                    float x[8];
+            }
+            u32x2_t cw, cm, cv;
+            u32x4_t wn, mn, vn;
+            if constexpr (WF8) {
+                float x[8];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) x[e] = wo[e] * w_inv;
-                    st_nt<u32x2_t>(reinterpret_cast<uint8_t *>(a.W) + off, Fp8::encode8(x));
-                } else {
-                    u32x4_t wn;
+                for (int e = 0; e < 8; ++e) x[e] = wo[e] * w_inv;
+                cw = Fp8::encode8(x);
+            } else {
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) wn[k] = pack_bf16(wo[2 * k], wo[2 * k + 1]);
-                    st_nt<u32x4_t>(a.W + off, wn);
+                for (int k = 0; k < 4; ++k) wn[k] = pack_bf16(wo[2 * k], wo[2 * k + 1]);
+            }
+            if constexpr (MF8) {
+                // sqrt(v') > 0 never stores as zero: clamped from below to the smallest code's
+                // 2^-9, which is also what anything above the tie at 2^-10 rounds to
+                float xm[8], xv[8], lo[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    xm[e] = mo[e] * m_inv;
+                    xv[e] = ro[e] * v_inv;
+                    lo[e] = ro[e] > 0.0f ? 0.001953125f : -448.0f;
                 }
+                cm = Fp8::encode8(xm);
+                cv = Fp8::encode8(xv, lo);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    mn[k] = pack_bf16(mo[2 * k], mo[2 * k + 1]);
+                    vn[k] = pack_bf16(vo[2 * k], vo[2 * k + 1]);
+                }
+            }
+            if (ok) {
+                const size_t off = (size_t)p * a.d_in + q;
+                if constexpr (WF8) st_nt<u32x2_t>(reinterpret_cast<uint8_t *>(a.W) + off, cw);
+                else st_nt<u32x4_t>(a.W + off, wn);
                 if constexpr (MF8) {
-                    float xm[8], xv[8];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        xm[e] = mo[e] * m_inv;
-                        xv[e] = ro[e] * v_inv;
-                    }
-                    u32x2_t cv = Fp8::encode8(xv);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)      // sqrt(v') > 0 never stores as zero
-                        if (ro[e] > 0.0f && ((cv[e >> 2] >> (8 * (e & 3))) & 0x7Fu) == 0u)
-                            cv[e >> 2] |= 1u << (8 * (e & 3));
-                    st_nt<u32x2_t>(static_cast<uint8_t *>(a.m) + off, Fp8::encode8(xm));
+                    st_nt<u32x2_t>(static_cast<uint8_t *>(a.m) + off, cm);
                     st_nt<u32x2_t>(static_cast<uint8_t *>(a.v) + off, cv);
                 } else {
-                    u32x4_t mn, vn;
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        mn[k] = pack_bf16(mo[2 * k], mo[2 * k + 1]);
-                        vn[k] = pack_bf16(vo[2 * k], vo[2 * k + 1]);
-                    }
                     st_nt<u32x4_t>(static_cast<uint16_t *>(a.m) + off, mn);
                     st_nt<u32x4_t>(static_cast<uint16_t *>(a.v) + off, vn);
                 }
             }
+            // close the pass: the maxima of several passes kept apart, or passes interleaved,
+            // spill past the 128 registers
+            asm volatile("" : "+v"(aw), "+v"(am), "+v"(av));
+            __builtin_amdgcn_sched_barrier(0);
         }
+        // the workgroup's maxima: each wave's, then one thread's over the four stream waves
         const int lane = s & 63;
-        if constexpr (WF8) Fp8::record(a.wr, wslot, aw, lane);
+        if constexpr (WF8) Fp8::put_max(amax, s >> 6, aw, lane);
         if constexpr (MF8) {
-            Fp8::record(a.ms, wslot, am, lane);
-            Fp8::record(a.vs, wslot, av, lane);
+            Fp8::put_max(amax + 4, s >> 6, am, lane);
+            Fp8::put_max(amax + 8, s >> 6, av, lane);
+        }
+        lds_barrier();
+        if constexpr (WF8) {
+            if (s == 0) Fp8::record(a.wr, wslot, amax);
+        }
+        if constexpr (MF8) {         // lanes of other waves: the three reads wait side by side
+            if (s == 64) Fp8::record(a.ms, wslot, amax + 4);
+            if (s == 128) Fp8::record(a.vs, wslot, amax + 8);
         }
         if (first_tile && s == 0) {
             const int clr = (a.slot + 1) % AMAX_SLOTS;
@@ -1228,8 +1293,10 @@ __global__ void __launch_bounds__(NT, 4) fused_kernel(GroupArgs g)
     using ML = Mainloop<BP, BQ, NSTAGE, TK128>;
     using EM = EpiMap<BP, BQ>;
     constexpr int MAIN = ML::LDS_BYTES > EM::GS_BYTES ? ML::LDS_BYTES : EM::GS_BYTES;
-    __shared__ __attribute__((aligned(16))) unsigned char smem[MAIN];
+    constexpr bool Q8 = IsEpiQ<typename EpiSel<BP, BQ, MK, EPI, AH>::T>::value;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[MAIN + (Q8 ? 64 : 0)];
     float *Gs = reinterpret_cast<float *>(smem);
+    int *amax = reinterpret_cast<int *>(smem + MAIN);
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1251,9 +1318,10 @@ __global__ void __launch_bounds__(NT, 4) fused_kernel(GroupArgs g)
         ml.run(a, p0, q0, smem, wave, lane, LEAD);
         ml.template stage_g<EM::GP>(Gs, wave, lane);
         lds_barrier();
+        if constexpr (Q8) lds_barrier();
     } else if constexpr (EPI != EPI_STORE_BF16 && EPI != EPI_STORE_F32) {
         typename EpiSel<BP, BQ, MK, EPI, AH>::T ep;
-        if constexpr (IsEpiQ<decltype(ep)>::value) ep.first_tile = (t == g.start[mi]);
+        if constexpr (Q8) ep.first_tile = (t == g.start[mi]);
         // The state prefetch leaves after the mainloop's first barrier (its first chunks'
         // DMA is then ahead of it); for the int8 row-block state, after the barriers of two
         // more chunks.  Measured at T = 512: the Llama-3.1-8B sweep 19.54-19.55 against
@@ -1265,7 +1333,8 @@ __global__ void __launch_bounds__(NT, 4) fused_kernel(GroupArgs g)
         ep.prefetch(a, p0, q0, s);
         for (; done < nbar; ++done) lds_barrier();
         lds_barrier();
-        ep.run(a, p0, q0, s, Gs);
+        if constexpr (Q8) ep.run(a, p0, q0, s, Gs, amax);
+        else ep.run(a, p0, q0, s, Gs);
     } else {
         for (int i = 0; i < nbar; ++i) lds_barrier();
         lds_barrier();
