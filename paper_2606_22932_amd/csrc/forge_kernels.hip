@@ -54,6 +54,8 @@ constexpr int I8_BLOCK = 256;   // rows of d_out sharing one int8 scale
 // block tall so that the block absmax closes inside the workgroup.
 constexpr int BP_F = 128, BQ_F = 128;
 constexpr int BP_I8 = 256, BQ_I8 = 64;
+// Tiles of the long-loop kernel.
+constexpr int BP_W = 128, BQ_W = 256;
 
 // ------------------------------------------------------------------------ small helpers
 
@@ -488,9 +490,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const void *base, uint
                                              __builtin_amdgcn_readfirstlane((int)n), 0x00020000);
 }
 
-template <int BP, int BQ, int MK, int E, int AH = 0>
+template <int BP, int BQ, int MK, int E, int AH = 0, int NTH = NROLE>
 struct EpiRule {
-    using M = EpiMap<BP, BQ>;
+    using M = EpiMap<BP, BQ, NTH>;
     using R = Rule<E>;
     static_assert(MK == MK_BF16 || MK == MK_F32, "the rule epilogue keeps bf16 or fp32 state");
     static constexpr bool F32 = (MK == MK_F32);
@@ -584,56 +586,63 @@ struct EpiRule {
         }
     }
 
-    __device__ __forceinline__ void run(const Args &a, int p0, int q0, int s, const float *Gs)
+    // Row pass i (a constant once the caller's loop is unrolled), its state in the registers.
+    __device__ __forceinline__ void pass(int i, const Args &a, const Hyper &h, int p0, int q0, int s,
+                                         const float *Gs)
     {
         const int rs = s / M::LPR, qo = (s % M::LPR) * 8, q = q0 + qo;
+        const int p = p0 + i * M::RPP + rs;
+        const bool ok = q < a.d_in && p < a.d_out;
+        const size_t off = (size_t)p * a.d_in + q;
+        const float *gr = Gs + (i * M::RPP + rs) * M::GP + qo;
+        const f32x4_t g0 = *reinterpret_cast<const f32x4_t *>(gr);
+        const f32x4_t g1 = *reinterpret_cast<const f32x4_t *>(gr + 4);
+        // W and the states stay packed until each element is needed
+        u32x4_t w4 = {0u, 0u, 0u, 0u}, a4 = w4, b4 = w4;
+        f32x4_t a0 = {0, 0, 0, 0}, a1 = a0, b0 = a0, b1 = a0;
+        if constexpr (F32) {
+            if constexpr (R::W_RW) w4 = pw[i];
+            if constexpr (R::NS >= 1) {
+                a0 = __builtin_bit_cast(f32x4_t, ps1[i][0]);
+                a1 = __builtin_bit_cast(f32x4_t, ps1[i][1]);
+            }
+            if constexpr (R::NS >= 2) {
+                b0 = __builtin_bit_cast(f32x4_t, ps2[i][0]);
+                b1 = __builtin_bit_cast(f32x4_t, ps2[i][1]);
+            }
+        } else {
+            if constexpr (R::W_RW) w4 = pw[i];
+            if constexpr (R::NS >= 1) a4 = ps1[i][0];
+            if constexpr (R::NS >= 2) b4 = ps2[i][0];
+        }
+        float wo[8], o1[8], o2[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float g = elt(g0, g1, e);
+            const float w = R::W_RW ? elt(w4, e) : 0.0f;
+            const float x = R::NS >= 1 ? (F32 ? elt(a0, a1, e) : elt(a4, e)) : 0.0f;
+            const float y = R::NS >= 2 ? (F32 ? elt(b0, b1, e) : elt(b4, e)) : 0.0f;
+            R::elem(g, w, x, y, h, wo[e], o1[e], o2[e]);
+        }
+        if (ok) {
+            if constexpr (R::W_RW) {
+                u32x4_t wn;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) wn[k] = pack_bf16(wo[2 * k], wo[2 * k + 1]);
+                st_nt<u32x4_t>(a.W + off, wn);
+            }
+            if constexpr (R::NS >= 1) store_state(a.m, off, o1);
+            if constexpr (R::NS >= 2) store_state(a.v, off, o2);
+        }
+    }
+
+    __device__ __forceinline__ void run(const Args &a, int p0, int q0, int s, const float *Gs)
+    {
         const Hyper h = a.h;
 #pragma unroll
         for (int i = 0; i < M::NPASS; ++i) {
             if (i + AHEAD < M::NPASS) prefetch_at(i + AHEAD, a, p0, q0, s);
-            const int p = p0 + i * M::RPP + rs;
-            const bool ok = q < a.d_in && p < a.d_out;
-            const size_t off = (size_t)p * a.d_in + q;
-            const float *gr = Gs + (i * M::RPP + rs) * M::GP + qo;
-            const f32x4_t g0 = *reinterpret_cast<const f32x4_t *>(gr);
-            const f32x4_t g1 = *reinterpret_cast<const f32x4_t *>(gr + 4);
-            // W and the states stay packed until each element is needed
-            u32x4_t w4 = {0u, 0u, 0u, 0u}, a4 = w4, b4 = w4;
-            f32x4_t a0 = {0, 0, 0, 0}, a1 = a0, b0 = a0, b1 = a0;
-            if constexpr (F32) {
-                if constexpr (R::W_RW) w4 = pw[i];
-                if constexpr (R::NS >= 1) {
-                    a0 = __builtin_bit_cast(f32x4_t, ps1[i][0]);
-                    a1 = __builtin_bit_cast(f32x4_t, ps1[i][1]);
-                }
-                if constexpr (R::NS >= 2) {
-                    b0 = __builtin_bit_cast(f32x4_t, ps2[i][0]);
-                    b1 = __builtin_bit_cast(f32x4_t, ps2[i][1]);
-                }
-            } else {
-                if constexpr (R::W_RW) w4 = pw[i];
-                if constexpr (R::NS >= 1) a4 = ps1[i][0];
-                if constexpr (R::NS >= 2) b4 = ps2[i][0];
-            }
-            float wo[8], o1[8], o2[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float g = elt(g0, g1, e);
-                const float w = R::W_RW ? elt(w4, e) : 0.0f;
-                const float x = R::NS >= 1 ? (F32 ? elt(a0, a1, e) : elt(a4, e)) : 0.0f;
-                const float y = R::NS >= 2 ? (F32 ? elt(b0, b1, e) : elt(b4, e)) : 0.0f;
-                R::elem(g, w, x, y, h, wo[e], o1[e], o2[e]);
-            }
-            if (ok) {
-                if constexpr (R::W_RW) {
-                    u32x4_t wn;
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) wn[k] = pack_bf16(wo[2 * k], wo[2 * k + 1]);
-                    st_nt<u32x4_t>(a.W + off, wn);
-                }
-                if constexpr (R::NS >= 1) store_state(a.m, off, o1);
-                if constexpr (R::NS >= 2) store_state(a.v, off, o2);
-            }
+            pass(i, a, h, p0, q0, s, Gs);
         }
     }
 };
@@ -703,9 +712,9 @@ __device__ __forceinline__ float div127(float x)
 // q = round_half_even(x * RN(1/s)) (the fp32 reciprocal of the scale, not a division)
 // clamped to [-127, 127], v codes at least 1 in a non-zero block.
 // The weight update reads the unquantised fp32 m', v'.
-template <int BP, int BQ>
+template <int BP, int BQ, int NTH = NROLE>
 struct EpiI8Row {
-    using M = EpiMap<BP, BQ>;
+    using M = EpiMap<BP, BQ, NTH>;
     static_assert(BQ % I8_ROW_BLOCK == 0 && M::LPR * 8 == BQ, "a block is 8 lanes of one row");
     u32x4_t pw[M::NPASS];
     u32x2_t pm[M::NPASS], pv[M::NPASS];
@@ -741,56 +750,61 @@ struct EpiI8Row {
         return (float)(int8_t)((c[e >> 2] >> (8 * (e & 3))) & 0xFFu);
     }
 
-    __device__ __forceinline__ void run(const Args &a, int p0, int q0, int s, const float *Gs)
+    // Row pass i (a constant once the caller's loop is unrolled), its state in the registers.
+    __device__ __forceinline__ void pass(int i, const Args &a, const Hyper &h, int p0, int q0, int s,
+                                         const float *Gs)
     {
         const int rs = s / M::LPR, qo = (s % M::LPR) * 8, q = q0 + qo;
-        const Hyper h = a.h;
+        const int p = p0 + i * M::RPP + rs;
+        const bool ok = q < a.d_in && p < a.d_out;
+        const float *gr = Gs + (i * M::RPP + rs) * M::GP + qo;
+        const f32x4_t g0 = *reinterpret_cast<const f32x4_t *>(gr);
+        const f32x4_t g1 = *reinterpret_cast<const f32x4_t *>(gr + 4);
+        float wo[8], mo[8], vo[8];
+        float am = 0.0f, av = 0.0f;
 #pragma unroll
-        for (int i = 0; i < M::NPASS; ++i) {
-            const int p = p0 + i * M::RPP + rs;
-            const bool ok = q < a.d_in && p < a.d_out;
-            const float *gr = Gs + (i * M::RPP + rs) * M::GP + qo;
-            const f32x4_t g0 = *reinterpret_cast<const f32x4_t *>(gr);
-            const f32x4_t g1 = *reinterpret_cast<const f32x4_t *>(gr + 4);
-            float wo[8], mo[8], vo[8];
-            float am = 0.0f, av = 0.0f;
+        for (int e = 0; e < 8; ++e) {
+            const float g = e < 4 ? g0[e] : g1[e - 4];
+            const float w = (e & 1) ? bf_hi(pw[i][e >> 1]) : bf_lo(pw[i][e >> 1]);
+            float rv;
+            adamw_elem(g, w, sm[i] * code_at(pm[i], e), sv[i] * code_at(pv[i], e), h, wo[e], mo[e], vo[e], rv);
+            am = fmaxf(am, fabsf(mo[e]));
+            av = fmaxf(av, vo[e]);
+        }
+        if (!ok) am = av = 0.0f;
+        am = max8(am);
+        av = max8(av);
+        const float scm = div127(am), scv = div127(av);
+        const float rcm = scm > 0.0f ? __builtin_amdgcn_rcpf(scm) : 0.0f;
+        const float rcv = scv > 0.0f ? __builtin_amdgcn_rcpf(scv) : 0.0f;
+        float ym[8], yv[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float g = e < 4 ? g0[e] : g1[e - 4];
-                const float w = (e & 1) ? bf_hi(pw[i][e >> 1]) : bf_lo(pw[i][e >> 1]);
-                float rv;
-                adamw_elem(g, w, sm[i] * code_at(pm[i], e), sv[i] * code_at(pv[i], e), h, wo[e], mo[e], vo[e], rv);
-                am = fmaxf(am, fabsf(mo[e]));
-                av = fmaxf(av, vo[e]);
-            }
-            if (!ok) am = av = 0.0f;
-            am = max8(am);
-            av = max8(av);
-            const float scm = div127(am), scv = div127(av);
-            const float rcm = scm > 0.0f ? __builtin_amdgcn_rcpf(scm) : 0.0f;
-            const float rcv = scv > 0.0f ? __builtin_amdgcn_rcpf(scv) : 0.0f;
-            float ym[8], yv[8];
+        for (int e = 0; e < 8; ++e) {
+            ym[e] = mo[e] * rcm;
+            yv[e] = vo[e] * rcv;
+        }
+        const u32x2_t cm = pack_codes(ym, -127.0f), cv = pack_codes(yv, rcv > 0.0f ? 1.0f : 0.0f);
+        if (ok) {
+            const size_t off = (size_t)p * a.d_in + q;
+            u32x4_t wn;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                ym[e] = mo[e] * rcm;
-                yv[e] = vo[e] * rcv;
-            }
-            const u32x2_t cm = pack_codes(ym, -127.0f), cv = pack_codes(yv, rcv > 0.0f ? 1.0f : 0.0f);
-            if (ok) {
-                const size_t off = (size_t)p * a.d_in + q;
-                u32x4_t wn;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) wn[k] = pack_bf16(wo[2 * k], wo[2 * k + 1]);
-                st_nt<u32x4_t>(a.W + off, wn);
-                st_nt<u32x2_t>(static_cast<int8_t *>(a.m) + off, cm);
-                st_nt<u32x2_t>(static_cast<int8_t *>(a.v) + off, cv);
-                if ((s & 7) == 0) {
-                    const size_t so = (size_t)p * nblocks(a) + q / I8_ROW_BLOCK;
-                    a.ms[so] = scm;
-                    a.vs[so] = scv;
-                }
+            for (int k = 0; k < 4; ++k) wn[k] = pack_bf16(wo[2 * k], wo[2 * k + 1]);
+            st_nt<u32x4_t>(a.W + off, wn);
+            st_nt<u32x2_t>(static_cast<int8_t *>(a.m) + off, cm);
+            st_nt<u32x2_t>(static_cast<int8_t *>(a.v) + off, cv);
+            if ((s & 7) == 0) {
+                const size_t so = (size_t)p * nblocks(a) + q / I8_ROW_BLOCK;
+                a.ms[so] = scm;
+                a.vs[so] = scv;
             }
         }
+    }
+
+    __device__ __forceinline__ void run(const Args &a, int p0, int q0, int s, const float *Gs)
+    {
+        const Hyper h = a.h;
+#pragma unroll
+        for (int i = 0; i < M::NPASS; ++i) pass(i, a, h, p0, q0, s, Gs);
     }
 };
 
@@ -874,9 +888,9 @@ struct Fp8 {
 // constants, one median per clamp and maxima recorded once per workgroup take the fp8
 // weight + moment step on 14336 x 4096 at T = 512 from 136 to 126 us, on 4096 x 4096 from
 // 45.2 to 39.8 us (fp8 moments 140 to 137 us and, on 4096 x 14336, 147 to 137 us).
-template <int BP, int BQ, bool WF8, bool MF8>
+template <int BP, int BQ, bool WF8, bool MF8, int NTH = NROLE>
 struct EpiQ {
-    using M = EpiMap<BP, BQ>;
+    using M = EpiMap<BP, BQ, NTH>;
     static constexpr int N16W = WF8 ? 1 : M::NPASS, N8W = WF8 ? M::NPASS : 1;
     static constexpr int N16M = MF8 ? 1 : M::NPASS, N8M = MF8 ? M::NPASS : 1;
     u32x4_t pw16[N16W], pm16[N16M], pv16[N16M];
@@ -920,13 +934,14 @@ struct EpiQ {
         return (e & 1) ? bf_hi(u[e >> 1]) : bf_lo(u[e >> 1]);
     }
 
-    // Contains one barrier, which the math waves also execute.
-    __device__ __forceinline__ void run(const Args &a, int p0, int q0, int s, const float *Gs, int *amax)
+    Hyper hk;                      // the recurrence's constants with the decode scales folded in
+    float w_inv, m_inv, v_inv;     // encode factors
+    float aw, am, av;              // maxima so far
+
+    __device__ __forceinline__ void begin(const Args &a)
     {
-        const int rs = s / M::LPR, qo = (s % M::LPR) * 8, q = q0 + qo;
-        const Hyper h = a.h;
-        const int wslot = a.slot, enc = (a.slot + 3) % AMAX_SLOTS, dec = (a.slot + 2) % AMAX_SLOTS;
-        float w_dec = 1.0f, w_inv = 1.0f, m_dec = 1.0f, m_inv = 1.0f, v_dec = 1.0f, v_inv = 1.0f;
+        const int enc = (a.slot + 3) % AMAX_SLOTS, dec = (a.slot + 2) % AMAX_SLOTS;
+        float w_dec = 1.0f, m_dec = 1.0f, v_dec = 1.0f;
         if constexpr (WF8) {
             w_dec = Fp8::scale_of(a.wr[dec]);
             w_inv = 1.0f / Fp8::scale_of(a.wr[enc]);
@@ -939,108 +954,114 @@ struct EpiQ {
         }
         // A decode scale multiplies its code by way of the recurrence's constant: m' = (b1 s)
         // q + c1 g, v' = (b2 s^2) q^2 + c2 g^2 (q^2 is exact), W' = (wdf s) q - update.
-        const float kw = WF8 ? h.wdf * w_dec : h.wdf;
-        const float km = MF8 ? h.b1 * m_dec : h.b1;
-        const float kv = MF8 ? h.b2 * v_dec * v_dec : h.b2;
-        float aw = 0.0f, am = 0.0f, av = 0.0f;
+        hk = a.h;
+        hk.wdf = WF8 ? a.h.wdf * w_dec : a.h.wdf;
+        hk.b1 = MF8 ? a.h.b1 * m_dec : a.h.b1;
+        hk.b2 = MF8 ? a.h.b2 * v_dec * v_dec : a.h.b2;
+        aw = am = av = 0.0f;
+    }
+
+    // Row pass i (a constant once the caller's loop is unrolled), its state in the registers.
+    __device__ __forceinline__ void pass(int i, const Args &a, const Hyper &, int p0, int q0, int s,
+                                         const float *Gs)
+    {
+        const int rs = s / M::LPR, qo = (s % M::LPR) * 8, q = q0 + qo;
+        const int p = p0 + i * M::RPP + rs;
+        const bool ok = q < a.d_in && p < a.d_out;
+        const float *gr = Gs + (i * M::RPP + rs) * M::GP + qo;
+        const f32x4_t g0 = *reinterpret_cast<const f32x4_t *>(gr);
+        const f32x4_t g1 = *reinterpret_cast<const f32x4_t *>(gr + 4);
+        float w0[8], m0[8], v0[8], wo[8], mo[8], vo[8], ro[8];
+        if constexpr (WF8) Fp8::decode8(pw8[i], w0);
+        if constexpr (MF8) {
+            Fp8::decode8(pm8[i], m0);
+            Fp8::decode8(pv8[i], v0);
+        }
 #pragma unroll
-        for (int i = 0; i < M::NPASS; ++i) {
-            const int p = p0 + i * M::RPP + rs;
-            const bool ok = q < a.d_in && p < a.d_out;
-            const float *gr = Gs + (i * M::RPP + rs) * M::GP + qo;
-            const f32x4_t g0 = *reinterpret_cast<const f32x4_t *>(gr);
-            const f32x4_t g1 = *reinterpret_cast<const f32x4_t *>(gr + 4);
-            float w0[8], m0[8], v0[8], wo[8], mo[8], vo[8], ro[8];
-            if constexpr (WF8) Fp8::decode8(pw8[i], w0);
+        for (int e = 0; e < 8; ++e) {
+            const float g = e < 4 ? g0[e] : g1[e - 4];
+            if constexpr (!WF8) w0[e] = bf(pw16[i], e);
             if constexpr (MF8) {
-                Fp8::decode8(pm8[i], m0);
-                Fp8::decode8(pv8[i], v0);
+                v0[e] *= v0[e];
+            } else {
+                m0[e] = bf(pm16[i], e);
+                v0[e] = bf(pv16[i], e);
             }
+            adamw_elem(g, w0[e], m0[e], v0[e], hk, wo[e], mo[e], vo[e], ro[e]);
+            // elements outside the matrix are zero here and leave the maxima alone
+            if constexpr (WF8) aw = fmaxf(aw, fabsf(wo[e]));
+            if constexpr (MF8) {
+                am = fmaxf(am, fabsf(mo[e]));
+                av = fmaxf(av, ro[e]);
+            }
+        }
+        u32x2_t cw, cm, cv;
+        u32x4_t wn, mn, vn;
+        if constexpr (WF8) {
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = wo[e] * w_inv;
+            cw = Fp8::encode8(x);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) wn[k] = pack_bf16(wo[2 * k], wo[2 * k + 1]);
+        }
+        if constexpr (MF8) {
+            // sqrt(v') > 0 never stores as zero: clamped from below to the smallest code's
+            // 2^-9, which is also what anything above the tie at 2^-10 rounds to
+            float xm[8], xv[8], lo[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const float g = e < 4 ? g0[e] : g1[e - 4];
-                if constexpr (!WF8) w0[e] = bf(pw16[i], e);
-                if constexpr (MF8) {
-                    v0[e] *= v0[e];
-                } else {
-                    m0[e] = bf(pm16[i], e);
-                    v0[e] = bf(pv16[i], e);
-                }
-                Hyper hk = h;
-                hk.b1 = km;
-                hk.b2 = kv;
-                hk.wdf = kw;
-                adamw_elem(g, w0[e], m0[e], v0[e], hk, wo[e], mo[e], vo[e], ro[e]);
-                // elements outside the matrix are zero here and leave the maxima alone
-                if constexpr (WF8) aw = fmaxf(aw, fabsf(wo[e]));
-                if constexpr (MF8) {
-                    am = fmaxf(am, fabsf(mo[e]));
-                    av = fmaxf(av, ro[e]);
-                }
+                xm[e] = mo[e] * m_inv;
+                xv[e] = ro[e] * v_inv;
+                lo[e] = ro[e] > 0.0f ? 0.001953125f : -448.0f;
             }
-            u32x2_t cw, cm, cv;
-            u32x4_t wn, mn, vn;
-            if constexpr (WF8) {
-                float x[8];
+            cm = Fp8::encode8(xm);
+            cv = Fp8::encode8(xv, lo);
+        } else {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) x[e] = wo[e] * w_inv;
-                cw = Fp8::encode8(x);
-            } else {
-#pragma unroll
-                for (int k = 0; k < 4; ++k) wn[k] = pack_bf16(wo[2 * k], wo[2 * k + 1]);
+            for (int k = 0; k < 4; ++k) {
+                mn[k] = pack_bf16(mo[2 * k], mo[2 * k + 1]);
+                vn[k] = pack_bf16(vo[2 * k], vo[2 * k + 1]);
             }
-            if constexpr (MF8) {
-                // sqrt(v') > 0 never stores as zero: clamped from below to the smallest code's
-                // 2^-9, which is also what anything above the tie at 2^-10 rounds to
-                float xm[8], xv[8], lo[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    xm[e] = mo[e] * m_inv;
-                    xv[e] = ro[e] * v_inv;
-                    lo[e] = ro[e] > 0.0f ? 0.001953125f : -448.0f;
-                }
-                cm = Fp8::encode8(xm);
-                cv = Fp8::encode8(xv, lo);
-            } else {
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    mn[k] = pack_bf16(mo[2 * k], mo[2 * k + 1]);
-                    vn[k] = pack_bf16(vo[2 * k], vo[2 * k + 1]);
-                }
-            }
-            if (ok) {
-                const size_t off = (size_t)p * a.d_in + q;
-                if constexpr (WF8) st_nt<u32x2_t>(reinterpret_cast<uint8_t *>(a.W) + off, cw);
-                else st_nt<u32x4_t>(a.W + off, wn);
-                if constexpr (MF8) {
-                    st_nt<u32x2_t>(static_cast<uint8_t *>(a.m) + off, cm);
-                    st_nt<u32x2_t>(static_cast<uint8_t *>(a.v) + off, cv);
-                } else {
-                    st_nt<u32x4_t>(static_cast<uint16_t *>(a.m) + off, mn);
-                    st_nt<u32x4_t>(static_cast<uint16_t *>(a.v) + off, vn);
-                }
-            }
-            // close the pass: the maxima of several passes kept apart, or passes interleaved,
-            // spill past the 128 registers
-            asm volatile("" : "+v"(aw), "+v"(am), "+v"(av));
-            __builtin_amdgcn_sched_barrier(0);
         }
-        // the workgroup's maxima: each wave's, then one thread's over the four stream waves
-        const int lane = s & 63;
-        if constexpr (WF8) Fp8::put_max(amax, s >> 6, aw, lane);
+        if (ok) {
+            const size_t off = (size_t)p * a.d_in + q;
+            if constexpr (WF8) st_nt<u32x2_t>(reinterpret_cast<uint8_t *>(a.W) + off, cw);
+            else st_nt<u32x4_t>(a.W + off, wn);
+            if constexpr (MF8) {
+                st_nt<u32x2_t>(static_cast<uint8_t *>(a.m) + off, cm);
+                st_nt<u32x2_t>(static_cast<uint8_t *>(a.v) + off, cv);
+            } else {
+                st_nt<u32x4_t>(static_cast<uint16_t *>(a.m) + off, mn);
+                st_nt<u32x4_t>(static_cast<uint16_t *>(a.v) + off, vn);
+            }
+        }
+        // close the pass: the maxima of several passes kept apart, or passes interleaved,
+        // spill past the 128 registers
+        asm volatile("" : "+v"(aw), "+v"(am), "+v"(av));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
+    // Record the maxima of the workgroup's NTH-wide epilogue (wave w of it, lane): contains one
+    // barrier, which every wave of the workgroup must execute.
+    __device__ __forceinline__ void finish(const Args &a, int w, int lane, int *amax)
+    {
+        if constexpr (WF8) Fp8::put_max(amax, w, aw, lane);
         if constexpr (MF8) {
-            Fp8::put_max(amax + 4, s >> 6, am, lane);
-            Fp8::put_max(amax + 8, s >> 6, av, lane);
+            Fp8::put_max(amax + 4, w, am, lane);
+            Fp8::put_max(amax + 8, w, av, lane);
         }
         lds_barrier();
+        if (lane != 0) return;
         if constexpr (WF8) {
-            if (s == 0) Fp8::record(a.wr, wslot, amax);
+            if (w == 0) Fp8::record(a.wr, a.slot, amax);
         }
         if constexpr (MF8) {         // lanes of other waves: the three reads wait side by side
-            if (s == 64) Fp8::record(a.ms, wslot, amax + 4);
-            if (s == 128) Fp8::record(a.vs, wslot, amax + 8);
+            if (w == 1) Fp8::record(a.ms, a.slot, amax + 4);
+            if (w == 2) Fp8::record(a.vs, a.slot, amax + 8);
         }
-        if (first_tile && s == 0) {
+        if (first_tile && w == 0) {
             const int clr = (a.slot + 1) % AMAX_SLOTS;
             if constexpr (WF8) a.wr[clr] = 0.0f;
             if constexpr (MF8) {
@@ -1049,18 +1070,32 @@ struct EpiQ {
             }
         }
     }
+
+    // Contains finish()'s barrier, which the math waves also execute.
+    __device__ __forceinline__ void run(const Args &a, int p0, int q0, int s, const float *Gs, int *amax)
+    {
+        begin(a);
+#pragma unroll
+        for (int i = 0; i < M::NPASS; ++i) pass(i, a, a.h, p0, q0, s, Gs);
+        finish(a, s >> 6, s & 63, amax);
+    }
 };
 
 template <class T> struct IsEpiQ { static constexpr bool value = false; };
-template <int BP, int BQ, bool W, bool M> struct IsEpiQ<EpiQ<BP, BQ, W, M>> { static constexpr bool value = true; };
+template <int BP, int BQ, bool W, bool M, int N> struct IsEpiQ<EpiQ<BP, BQ, W, M, N>> { static constexpr bool value = true; };
 
 // The epilogue of (moment kind, rule): the row-block int8 layout and the fp8 encodings have
 // their own (AdamW only).
-template <int BP, int BQ, int MK, int E, int AH = 0> struct EpiSel { using T = EpiRule<BP, BQ, MK, E, AH>; };
-template <int BP, int BQ> struct EpiSel<BP, BQ, MK_I8R64, EPI_ADAMW> { using T = EpiI8Row<BP, BQ>; };
-template <int BP, int BQ> struct EpiSel<BP, BQ, MK_FP8, EPI_ADAMW> { using T = EpiQ<BP, BQ, false, true>; };
-template <int BP, int BQ> struct EpiSel<BP, BQ, MK_BF16, EPI_ADAMW_WFP8> { using T = EpiQ<BP, BQ, true, false>; };
-template <int BP, int BQ> struct EpiSel<BP, BQ, MK_FP8, EPI_ADAMW_WFP8> { using T = EpiQ<BP, BQ, true, true>; };
+template <int BP, int BQ, int MK, int E, int AH = 0, int N = NROLE>
+struct EpiSel { using T = EpiRule<BP, BQ, MK, E, AH, N>; };
+template <int BP, int BQ, int AH, int N>
+struct EpiSel<BP, BQ, MK_I8R64, EPI_ADAMW, AH, N> { using T = EpiI8Row<BP, BQ, N>; };
+template <int BP, int BQ, int AH, int N>
+struct EpiSel<BP, BQ, MK_FP8, EPI_ADAMW, AH, N> { using T = EpiQ<BP, BQ, false, true, N>; };
+template <int BP, int BQ, int AH, int N>
+struct EpiSel<BP, BQ, MK_BF16, EPI_ADAMW_WFP8, AH, N> { using T = EpiQ<BP, BQ, true, false, N>; };
+template <int BP, int BQ, int AH, int N>
+struct EpiSel<BP, BQ, MK_FP8, EPI_ADAMW_WFP8, AH, N> { using T = EpiQ<BP, BQ, true, true, N>; };
 
 // AdamW on int8 block-absmax moments (App. B scheme; blocks of 256 rows along d_out,
 // second moment stored through its square root, codes of v floored at 1).  The tile is
@@ -1339,6 +1374,285 @@ __global__ void __launch_bounds__(NT, 4) fused_kernel(GroupArgs g)
         for (int i = 0; i < nbar; ++i) lds_barrier();
         lds_barrier();
         epi_store_g<BP, BQ, EPI == EPI_STORE_F32>(a, p0, q0, s, Gs);
+    }
+}
+
+// ------------------------------------------------ 128 x 256 tiles for long token loops
+//
+// With many tokens the step is a matrix product with an epilogue, and the 128 x 128 kernel
+// above is bound by its operand DMA: per tile and 32 tokens 16 KB for 2^19 multiply-adds (on
+// 28672 x 4096 at T = 4096 the DMA alone takes 1.01 ms of its loop's 1.09 ms, the matrix
+// instructions 0.42 ms).  A 128 x 256 tile moves 12 KB for as many.  One workgroup of four
+// waves (64 rows x 128 columns each) owns a tile, two are resident per CU, one wave of each
+// on every SIMD, and every wave runs the epilogue of its own part: while one workgroup streams
+// state, the other's products run.  Measured against the 128 x 128 kernel (bf16 state,
+// AdamW): 28672 x 4096 at T = 4096 978 against 1260 us, 14336 x 4096 502 against 650 us, at
+// T = 2048 298 against 327 us, at T = 512 the same.  256 x 256 tiles (one workgroup of eight
+// waves per CU) are 1-5 % slower except on the longest loops: nothing covers their epilogue.
+//
+// Token loop: a ring of three 24 KB stages (32 tokens).  The fragments of a 16-token step are
+// read from LDS while the matrix instructions of the step before run, across chunks too; one
+// barrier per chunk, in the middle of its products: behind it the next chunk has landed for
+// every wave, and the stage that it frees is refilled.
+template <int BP_, int BQ_>
+struct WideLoop {
+    static constexpr int BP = BP_, BQ = BQ_, TK = 32, NS = 3;
+    static constexpr int WP = BP / 64, WQ = BQ / 128, NW = WP * WQ;
+    static_assert(NW == 4, "four waves of 64 x 128");
+    static constexpr int NA = 4, NB = 2;                 // 32-column and 32-row blocks of a wave
+    static constexpr int XROWB = BQ * 2, YROWB = BP * 2; // LDS bytes per token row
+    static constexpr int XB = TK * XROWB, YB = TK * YROWB;
+    static constexpr int STAGE = XB + YB;
+    static constexpr int XI = XB / 1024 / NW, DPC = STAGE / 1024 / NW;   // DMA instructions per wave and chunk
+    static_assert(XB % (1024 * NW) == 0 && YB % (1024 * NW) == 0, "a wave's k-th DMA is all X or all dY");
+    static_assert(XROWB >= 256 && YROWB >= 256, "the swizzle assumes rows of at least 256 bytes");
+
+    f32x16_t acc[NA][NB];
+    uint32_t voff[DPC], ta[NA], tb[NB];
+
+    // as Mainloop::swz for rows of at least 256 bytes
+    static __device__ __forceinline__ int swz(int t) { return 4 * (t & 3); }
+
+    __device__ __forceinline__ void setup(const Args &a, int p0, int q0, int wave, int lane)
+    {
+#pragma unroll
+        for (int k = 0; k < DPC; ++k) {
+            const bool x = k < XI;
+            const int L = ((x ? k : k - XI) * NW + wave) * 64 + lane;    // 16-byte piece of X or dY
+            const int ppr = (x ? XROWB : YROWB) / 16;
+            const int t = L / ppr;
+            const int ld = x ? a.d_in : a.d_out;
+            const int col = (x ? q0 : p0) + 8 * ((L % ppr) ^ swz(t));
+            const uint64_t off = ((uint64_t)t * (uint64_t)ld + (uint64_t)col) * 2u;
+            voff[k] = (col < ld && off < OOR_OFFSET) ? (uint32_t)off : OOR_OFFSET;
+        }
+        const int wq = wave % WQ, wp = wave / WQ;
+        const int s = lane & 15;
+        const int trow = 8 * (lane >> 5) + (s >> 2);
+        const int low = 2 * ((lane >> 4) & 1) + ((s & 3) >> 1), half = (s & 1) * 8;
+#pragma unroll
+        for (int i = 0; i < NA; ++i) ta[i] = trow * XROWB + ((wq * 16 + i * 4 + low) ^ swz(trow)) * 16 + half;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) tb[j] = XB + trow * YROWB + ((wp * 8 + j * 4 + low) ^ swz(trow)) * 16 + half;
+    }
+
+    // DMA of token chunk c into its stage (see Mainloop::issue).
+    __device__ __forceinline__ void issue(const Args &a, unsigned char *lds, int c, int wave)
+    {
+        unsigned char *stage = lds + (c % NS) * STAGE;
+        const int rows = min(TK, a.T - c * TK);
+        const size_t r0 = (size_t)c * TK;
+        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint16_t *>(a.X + r0 * (size_t)a.d_in), (short)0,
+            (int)((uint32_t)rows * (uint32_t)a.d_in * 2u), 0x00020000);
+        const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint16_t *>(a.dY + r0 * (size_t)a.d_out), (short)0,
+            (int)((uint32_t)rows * (uint32_t)a.d_out * 2u), 0x00020000);
+#pragma unroll
+        for (int k = 0; k < DPC; ++k) {
+            auto *dst = (__attribute__((address_space(3))) void *)(stage + (k * NW + wave) * 1024);
+            if (k < XI) __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, dst, 16, voff[k], 0, 0, 0);
+            else __builtin_amdgcn_raw_ptr_buffer_load_lds(ry, dst, 16, voff[k], 0, 0, 0);
+        }
+    }
+
+    // The fragments of one 16-token step.  They are in flight until settle().
+    struct Frags {
+        v4i16_t a[NA][2], b[NB][2];                      // [block][token half]
+    };
+
+    template <int OFF>
+    static __device__ __forceinline__ void tr_read(v4i16_t &r, uint32_t addr)
+    {
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "i"(OFF) : "memory");
+    }
+
+    template <int STEP>
+    __device__ __forceinline__ void read(Frags &f, uint32_t st) const
+    {
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            tr_read<16 * STEP * YROWB>(f.b[j][0], st + tb[j]);
+            tr_read<(16 * STEP + 4) * YROWB>(f.b[j][1], st + tb[j]);
+        }
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            tr_read<16 * STEP * XROWB>(f.a[i][0], st + ta[i]);
+            tr_read<(16 * STEP + 4) * XROWB>(f.a[i][1], st + ta[i]);
+        }
+    }
+
+    // Wait for the fragments (they are the only LDS reads in flight).
+    static __device__ __forceinline__ void settle(Frags &f)
+    {
+        asm volatile("s_waitcnt lgkmcnt(0)"
+                     : "+v"(f.a[0][0]), "+v"(f.a[0][1]), "+v"(f.a[1][0]), "+v"(f.a[1][1]), "+v"(f.a[2][0]),
+                       "+v"(f.a[2][1]), "+v"(f.a[3][0]), "+v"(f.a[3][1]), "+v"(f.b[0][0]), "+v"(f.b[0][1]),
+                       "+v"(f.b[1][0]), "+v"(f.b[1][1])
+                     :
+                     : "memory");
+    }
+
+    static __device__ __forceinline__ bf16x8_t cat(v4i16_t lo, v4i16_t hi)
+    {
+        return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+
+    __device__ __forceinline__ void mma(const Frags &f)
+    {
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cat(f.a[i][0], f.a[i][1]), cat(f.b[j][0], f.b[j][1]),
+                                                                     acc[i][j], 0, 0, 0);
+    }
+
+    // Wait until at most `younger` (0..2) chunks issued after the awaited one are in flight.
+    // Older stores count too, and can only make the wait longer.
+    static __device__ __forceinline__ void wait_dma(int younger)
+    {
+        static_assert(NS == 3, "at most two younger chunks");
+        if (younger >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"i"(2 * DPC) : "memory");
+        else if (younger == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"i"(DPC) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+
+    // The token loop.  `tail` runs once every DMA of the tile has landed, before the last
+    // products: global loads that it issues are in flight with nothing behind them.
+    template <class F>
+    __device__ __forceinline__ void run(const Args &a, int p0, int q0, unsigned char *lds, int wave, int lane, F tail)
+    {
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+        const int nch = (a.T + TK - 1) / TK;
+        if (nch == 0) {
+            tail();
+            return;
+        }
+        setup(a, p0, q0, wave, lane);
+#pragma unroll
+        for (int c = 0; c < NS; ++c)
+            if (c < nch) issue(a, lds, c, wave);
+        const uint32_t base = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)lds;
+        Frags f0, f1;
+        wait_dma(min(NS - 1, nch - 1));
+        asm volatile("s_barrier" ::: "memory");
+        read<0>(f0, base);
+        settle(f0);
+        for (int c = 0; c + 1 < nch; ++c) {
+            read<1>(f1, base + (uint32_t)((c % NS) * STAGE));
+            mma(f0);
+            __builtin_amdgcn_sched_barrier(0);
+            wait_dma(min(NS - 2, nch - 2 - c));
+            settle(f1);
+            // every wave has read stage c, and chunk c + 1 has landed
+            asm volatile("s_barrier" ::: "memory");
+            read<0>(f0, base + (uint32_t)(((c + 1) % NS) * STAGE));
+            if (c + NS < nch) issue(a, lds, c + NS, wave);
+            __builtin_amdgcn_sched_barrier(0);
+            mma(f1);
+            __builtin_amdgcn_sched_barrier(0);
+            settle(f0);
+        }
+        read<1>(f1, base + (uint32_t)(((nch - 1) % NS) * STAGE));
+        mma(f0);
+        __builtin_amdgcn_sched_barrier(0);
+        settle(f1);
+        tail();
+        mma(f1);
+    }
+
+    // Rows ip*32 .. +31 of this wave's part to LDS as G[p][q] (fp32, pitch GP floats).
+    template <int GP>
+    __device__ __forceinline__ void stage_g(float *Gs, int ip, int lane) const
+    {
+#pragma unroll
+        for (int iq = 0; iq < NA; ++iq)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const f32x16_t &x = acc[iq][ip];
+                const f32x4_t v = {x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]};
+                *reinterpret_cast<f32x4_t *>(Gs + (lane & 31) * GP + iq * 32 + g * 8 + (lane >> 5) * 4) = v;
+            }
+    }
+};
+
+// ep.prefetch_pass<i> for a pass index known once the caller's loop is unrolled.
+template <class EP, int I = 0>
+__device__ __forceinline__ void prefetch_at(EP &ep, int i, const Args &a, int p0, int q0, int s)
+{
+    if (i == I) ep.template prefetch_pass<I>(a, p0, q0, s);
+    else if constexpr (I + 1 < EP::M::NPASS) prefetch_at<EP, I + 1>(ep, i, a, p0, q0, s);
+}
+
+// Each wave streams the state of its 64 x 128 part in sixteen passes of four rows: unit 0 (the
+// first 32 rows) and unit 1, staged one after the other through the wave's own LDS region (no
+// barrier).  AH passes are in flight; a pass's registers take the pass AH later.  Fewer than
+// three cost 5-15 %, more than six spill.  A workgroup walks tiles blockIdx, blockIdx + gridDim,
+// ...: a new workgroup in a finished one's place comes 2.5 us later (of about 35 us a tile).
+template <int MK, int EPI>
+__global__ void __launch_bounds__(NROLE, 2) wide_kernel(GroupArgs g)
+{
+    using L = WideLoop<BP_W, BQ_W>;
+    using EP = typename EpiSel<32, 128, MK, EPI, 0, 64>::T;
+    constexpr bool Q8 = IsEpiQ<EP>::value;
+    using EM = typename EP::M;
+    constexpr int AH = MK == MK_F32 ? 3 : 6;             // passes in flight
+    constexpr int EARLY = AH < 4 ? AH : 4;               // of them, issued beside the last products
+    constexpr int MAIN = L::NS * L::STAGE > L::NW * EM::GS_BYTES ? L::NS * L::STAGE : L::NW * EM::GS_BYTES;
+    static_assert(EM::NPASS == 8, "a unit is eight passes");
+    __shared__ __attribute__((aligned(16))) unsigned char smem[MAIN + (Q8 ? 64 : 0)];
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int b = blockIdx.x; b < g.start[g.n]; b += gridDim.x) {
+        // Hidden from the compiler, which would otherwise keep what it derives from the lane
+        // number for all tiles, in registers that the tile needs.
+        int lane = tid & 63;
+        asm volatile("" : "+v"(lane));
+        const int t = xcd_remap(b, g.start[g.n]);
+        int mi = 0;
+        while (mi + 1 < g.n && t >= g.start[mi + 1]) ++mi;
+        const Args a = g.a[mi];
+        int tp, tq;
+        raster(t - g.start[mi], a.tiles_p, a.tiles_q, a.group_p, tp, tq);
+        const int p0 = tp * L::BP, q0 = tq * L::BQ;
+        const int pw = p0 + (wave / L::WQ) * 64, qw = q0 + (wave % L::WQ) * 128;
+
+        L ml;
+        EP ep;
+        ml.run(a, p0, q0, smem, wave, lane, [&]() {
+#pragma unroll
+            for (int i = 0; i < EARLY; ++i) prefetch_at(ep, i, a, pw, qw, lane);
+        });
+        lds_barrier();                                       // every wave is done reading the ring
+        float *Gs = reinterpret_cast<float *>(smem + wave * EM::GS_BYTES);
+        const Hyper h = a.h;
+        if constexpr (Q8) {
+            ep.first_tile = (t == g.start[mi]);
+            ep.begin(a);
+        }
+        ml.template stage_g<EM::GP>(Gs, 0, lane);
+#pragma unroll
+        for (int i = EARLY; i < AH; ++i) prefetch_at(ep, i, a, pw, qw, lane);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (u) ml.template stage_g<EM::GP>(Gs, 1, lane);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                ep.pass(i, a, h, pw + 32 * u, qw, lane, Gs);
+                const int nx = 8 * u + i + AH;
+                if (nx < 16) prefetch_at(ep, nx & 7, a, pw + 32 * (nx >> 3), qw, lane);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if constexpr (Q8) ep.finish(a, wave, lane, reinterpret_cast<int *>(smem + MAIN));
+        lds_barrier();                                   // the next tile's chunks overwrite the staged G
     }
 }
 
@@ -1793,36 +2107,67 @@ static Args with_grid(Args a, int bp, int bq, int &ntiles, int group_p = 0)
     return a;
 }
 
-// Tile grid of each matrix, prefix sums of their tile counts, and the launch.
-template <int BP, int BQ, int MK, int EPI>
-static hipError_t launch_group(const Args *a, int n, hipStream_t st)
+// Tile grids of n matrices in bp x bq tiles (raster groups of group_p tile rows, 0: by shape)
+// and the prefix sums of their tile counts.
+static GroupArgs group_of(const Args *a, int n, int bp, int bq, int group_p)
 {
     GroupArgs g;
     g.n = n;
     g.start[0] = 0;
     for (int i = 0; i < n; ++i) {
         int nt;
-        // int8 row-block state: groups of 8 tile rows (measured on the MLP projections at
-        // T = 512: 5 % faster than the shape rule, whose 24-row groups suit bf16 state)
-        g.a[i] = with_grid(a[i], BP, BQ, nt, MK == MK_I8R64 ? 8 : 0);
+        g.a[i] = with_grid(a[i], bp, bq, nt, group_p);
         g.start[i + 1] = g.start[i] + nt;
     }
     for (int i = n; i < MAX_GROUP; ++i) {
         g.a[i] = g.a[0];
         g.start[i + 1] = g.start[n];
     }
+    return g;
+}
+
+// Whether a launch of `tiles` 128 x 256 tiles with T tokens runs in wide_kernel, whose 2 * CUs
+// workgroups want at least two tiles each (measured over 2048-14336 wide shapes; ratio of the
+// 128 x 128 kernel's time to wide_kernel's).  T >= 1024: 1.02-1.10 (every rule and state; 14336
+// x 4096 with fp32 state 1.00), 1.25-1.30 at T = 4096; at T = 512 0.91-0.98 with bf16 and
+// fp32 state, but with 8-bit state, whose epilogue is short beside the loop, 1.00-1.12.  fp8
+// weights and moments gain from one tile per workgroup and T = 256 on (1.01-1.08).  With fewer
+// tiles the smaller tiles fill the chip better (2048 x 4096: 0.75-0.95).
+static bool wide_pays(int mk, int epi, int T, int tiles)
+{
+    const int slots = 2 * device_cu_count();
+    const bool w8 = epi == EPI_ADAMW_WFP8;
+    if (w8 && mk == MK_FP8) return T >= 256 && tiles >= slots;
+    if (tiles < 2 * slots) return false;
+    return T >= (w8 || mk == MK_I8R64 || mk == MK_FP8 ? 512 : 1024);
+}
+
+// The launch of n matrices (all with the same T).
+template <int BP, int BQ, int MK, int EPI>
+static hipError_t launch_group(const Args *a, int n, hipStream_t st)
+{
+    if constexpr (EPI != EPI_STORE_BF16 && EPI != EPI_STORE_F32) {
+        // raster groups of 8 tile rows: against 4, 1-8 % faster on 8192 x 8192, even elsewhere
+        const GroupArgs w = group_of(a, n, BP_W, BQ_W, 8);
+        const int tiles = w.start[n], slots = 2 * device_cu_count();
+        if (wide_pays(MK, EPI, a[0].T, tiles)) {
+            hipLaunchKernelGGL((wide_kernel<MK, EPI>), dim3(tiles < slots ? tiles : slots), dim3(NROLE), 0, st, w);
+            return hipGetLastError();
+        }
+    }
+    // int8 row-block state: groups of 8 tile rows (measured on the MLP projections at
+    // T = 512: 5 % faster than the shape rule, whose 24-row groups suit bf16 state)
+    const GroupArgs g = group_of(a, n, BP, BQ, MK == MK_I8R64 ? 8 : 0);
     if (g.start[n] == 0) return hipSuccess;
     // Prefetch depth by launch length (AdamW on bf16 state): a launch of at least 8 waves of
-    // resident tiles, or with a long token loop (T >= 1024 in every matrix), loads all eight
+    // resident tiles, or with a long token loop (T >= 1024), loads all eight
     // row passes of a tile's state during its mainloop, a shorter one six.  Measured per
     // launch group of the Llama-3.1-8B sweep at T = 512: lm_head (63 waves) 1157 against
     // 1222 us, gate+up (14) even, down (7), o (2) and q+k+v (3) 1-7 % slower with eight; on
     // 4096 x 4096 over three rotated copies, eight were 2-4.5 % faster at T = 1024-4096
     // (T = 4096: 145.9-146.4 against 148.9-149.1 us).
-    int min_t = a[0].T;
-    for (int i = 1; i < n; ++i) min_t = a[i].T < min_t ? a[i].T : min_t;
     if constexpr (MK == MK_BF16 && EPI == EPI_ADAMW)
-        if (g.start[n] >= 8 * 2 * device_cu_count() || min_t >= 1024) {
+        if (g.start[n] >= 8 * 2 * device_cu_count() || a[0].T >= 1024) {
             hipLaunchKernelGGL((fused_kernel<BP, BQ, MK, EPI, 8>), dim3(g.start[n]), dim3(NT), 0, st, g);
             return hipGetLastError();
         }
@@ -1859,23 +2204,13 @@ static int raster_rows_i8(int T)
     return g;
 }
 
-// int8 moments: one persistent workgroup per CU, tiles pipelined (pipelined_i8_kernel).
-static hipError_t launch_i8_pipelined(const Args *a, int n, hipStream_t st)
+// int8 moments in 256-row blocks.
+static hipError_t launch_i8(const Args *a, int n, hipStream_t st)
 {
-    GroupArgs g;
-    g.n = n;
-    g.start[0] = 0;
-    for (int i = 0; i < n; ++i) {
-        int nt;
-        g.a[i] = with_grid(a[i], BP_I8, BQ_I8, nt, raster_rows_i8(a[i].T));
-        g.start[i + 1] = g.start[i] + nt;
-    }
-    for (int i = n; i < MAX_GROUP; ++i) {
-        g.a[i] = g.a[0];
-        g.start[i + 1] = g.start[n];
-    }
+    const GroupArgs g = group_of(a, n, BP_I8, BQ_I8, raster_rows_i8(a[0].T));
     const int total = g.start[n];
     if (total == 0) return hipSuccess;
+    // one persistent workgroup per CU, its tiles pipelined
     const int ncu = device_cu_count();
     const int grid = total < ncu ? total : ncu;
     hipLaunchKernelGGL(pipelined_i8_kernel, dim3(grid), dim3(NT_I8P), 0, st, g);
@@ -1884,7 +2219,7 @@ static hipError_t launch_i8_pipelined(const Args *a, int n, hipStream_t st)
 
 hipError_t launch_fused_group(const Args *a, int n, int mk, hipStream_t st)
 {
-    if (mk == MK_I8) return launch_i8_pipelined(a, n, st);
+    if (mk == MK_I8) return launch_i8(a, n, st);
     if (mk == MK_I8R64) return launch_group<BP_F, BQ_F, MK_I8R64, EPI_ADAMW>(a, n, st);
     if (mk == MK_FP8) return launch_group<BP_F, BQ_F, MK_FP8, EPI_ADAMW>(a, n, st);
     if (mk == MK_BF16) return launch_group<BP_F, BQ_F, MK_BF16, EPI_ADAMW>(a, n, st);

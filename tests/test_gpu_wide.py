@@ -1,0 +1,138 @@
+"""The kernels for long token loops (128 x 256 tiles; 256 x 128 for int8 column blocks) against
+the 128 x 128 kernel, bit for bit.
+
+Steps are tile-local and every kernel sums a tile's products in the same order, so a matrix
+large enough for the long-loop kernel must end with the same bits as its row slices stepped one
+by one, which are too small for it; the kernel that steps the slices is checked against the
+oracle elsewhere.  Sizes leave remainders on every axis, more tiles than resident workgroups
+(a workgroup walks several tiles), and a last chunk of one token.
+"""
+import pytest
+import torch
+
+from gpu_util import HP
+from paper_2606_22932_amd import forge
+
+pytestmark = pytest.mark.gpu
+
+D_IN, D_OUT, SLICE = 4104, 8264, 1024      # 17 x 65 tiles of 256 columns x 128 rows; 33 x 33 of 128 x 256
+
+
+def _gauss(shape, std, gen, dtype=torch.bfloat16):
+    return torch.randn(shape, generator=gen, device="cuda").mul_(std).to(dtype)
+
+
+def _state(kind, rows, gen):
+    """State tensors of [rows, D_IN] by argument name."""
+    shape = (rows, D_IN)
+    codes = lambda lo, hi: torch.randint(lo, hi, shape, generator=gen, device="cuda", dtype=torch.int8)
+    fp8 = lambda lo, hi: torch.randint(lo, hi, shape, generator=gen, device="cuda",
+                                       dtype=torch.uint8).view(torch.float8_e4m3fn)
+    ring = lambda a: torch.tensor([0.0, 0.0, a, a], device="cuda")
+    s = {"W": _gauss(shape, 0.02, gen)}
+    if kind in ("bf16", "f32", "wfp8_bf16"):
+        dt = torch.float32 if kind == "f32" else torch.bfloat16
+        s["m"], s["v"] = _gauss(shape, 1e-4, gen, dt), _gauss(shape, 1e-6, gen, torch.float32).abs_().to(dt)
+    elif kind in ("i8", "i8r64"):
+        sshape = ((rows + 255) // 256, D_IN) if kind == "i8" else (rows, (D_IN + 63) // 64)
+        s["m"], s["v"] = codes(-127, 128), codes(1, 128)
+        u = lambda x: torch.rand(sshape, generator=gen, device="cuda").add_(0.5).mul_(x / 127)
+        s["ms"], s["vs"] = u(3e-4), u(3e-3 if kind == "i8" else 3e-6)
+    else:
+        s["m"], s["v"] = fp8(0, 0x7F), fp8(0, 0x7F)
+        s["ms"], s["vs"] = ring(3e-4), ring(3e-3)
+    if kind.startswith("wfp8"):
+        s["W"], s["wr"] = fp8(0, 0x7F), ring(0.06)
+    return s
+
+
+def _step(kind, X, dY, s):
+    if kind.startswith("wfp8"):
+        forge.forge_linear_step_wfp8(X, dY, s["W"], s["wr"], s["m"], s["v"], s.get("ms"), s.get("vs"), step=100, **HP)
+    else:
+        forge.forge_linear_step(X, dY, s["W"], s["m"], s["v"], s.get("ms"), s.get("vs"), step=100, **HP)
+
+
+def _rows(kind, name, t, r0, r1):
+    """The part of state tensor `name` that belongs to rows r0..r1 (a ring: all of it)."""
+    if t.shape == (4,):
+        return t
+    if kind == "i8" and name in ("ms", "vs"):
+        return t[r0 // 256:(r1 + 255) // 256]
+    return t[r0:r1]
+
+
+def _raw(t):
+    return t.view(torch.uint8) if t.dtype == torch.float8_e4m3fn else t
+
+
+@pytest.mark.parametrize("kind,T", [("bf16", 1025), ("f32", 1056), ("i8r64", 513), ("fp8", 544), ("wfp8_bf16", 545),
+                                    ("wfp8_fp8", 257), ("i8", 0), ("i8", 1), ("i8", 70), ("i8", 513)])
+def test_long_loop_kernel_equals_row_slices_bitwise(kind, T):
+    print("case", kind, T, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(11)
+    X, dY = _gauss((T, D_IN), 1.0, gen), _gauss((T, D_OUT), 1e-3, gen)
+    whole = _state(kind, D_OUT, gen)
+    parts = []
+    for r0 in range(0, D_OUT, SLICE):
+        r1 = min(r0 + SLICE, D_OUT)
+        parts.append((r0, r1, {k: _rows(kind, k, t, r0, r1).clone() for k, t in whole.items()}))
+    _step(kind, X, dY, whole)
+    for r0, r1, s in parts:
+        _step(kind, X, dY[:, r0:r1].contiguous(), s)
+    torch.cuda.synchronize()
+    for k, t in whole.items():
+        if t.shape == (4,):        # amax ring: this step's slot is the largest of the slices'
+            want = torch.stack([s[k] for _, _, s in parts]).amax(0)
+            assert torch.equal(t, want), k
+            continue
+        for r0, r1, s in parts:
+            assert torch.equal(_raw(_rows(kind, k, t, r0, r1)), _raw(s[k])), (k, r0)
+
+
+@pytest.mark.parametrize("rule,dtype", [("sgd_momentum", torch.float32), ("nadam", torch.bfloat16),
+                                        ("muon_accumulate", torch.bfloat16)])
+def test_long_loop_rules_equal_row_slices_bitwise(rule, dtype):
+    print("case", rule, dtype, flush=True)
+    T = 1031
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(12)
+    X, dY = _gauss((T, D_IN), 1.0, gen), _gauss((T, D_OUT), 1e-3, gen)
+    W = None if rule == "muon_accumulate" else _gauss((D_OUT, D_IN), 0.02, gen)
+    ns = forge.OPTIMIZER_STATES[rule]
+    st = [_gauss((D_OUT, D_IN), 1e-3, gen, torch.float32).abs_().to(dtype) for _ in range(ns)]
+    hp = dict(lr=1e-3, beta1=0.9, beta2=0.99, weight_decay=0.1, step=7)
+
+    def run(dY, W, st):
+        forge.forge_linear_step_opt(X, dY, W, *st, optimizer=rule, **hp)
+
+    ranges = [(r, min(r + SLICE, D_OUT)) for r in range(0, D_OUT, SLICE)]
+    parts = [(W if W is None else W[a:b].clone(), [t[a:b].clone() for t in st]) for a, b in ranges]
+    run(dY, W, st)
+    for (a, b), (w, ss) in zip(ranges, parts):
+        run(dY[:, a:b].contiguous(), w, ss)
+    torch.cuda.synchronize()
+    for (a, b), (w, ss) in zip(ranges, parts):
+        assert W is None or torch.equal(W[a:b], w), a
+        for t, u in zip(st, ss):
+            assert torch.equal(t[a:b], u), a
+
+
+def test_long_loop_group_equals_single_steps_bitwise():
+    """A group that only together is large enough for the long-loop kernel."""
+    T, d_in, d_outs = 1040, 2056, (7184, 264, 8200)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(13)
+    X = _gauss((T, d_in), 1.0, gen)
+    mats = []
+    for d in d_outs:
+        m, v = _gauss((d, d_in), 1e-4, gen), _gauss((d, d_in), 1e-6, gen).abs_()
+        mats.append((X, _gauss((T, d), 1e-3, gen), _gauss((d, d_in), 0.02, gen), m, v))
+    alone = [(X, b[1]) + tuple(t.clone() for t in b[2:]) for b in mats]
+    forge.forge_linear_step_grouped(mats, step=100, **HP)
+    for b in alone:
+        forge.forge_linear_step(*b, step=100, **HP)
+    torch.cuda.synchronize()
+    for x, y in zip(mats, alone):
+        assert all(torch.equal(s, t) for s, t in zip(x[2:], y[2:]))
