@@ -671,27 +671,30 @@ __device__ __forceinline__ float max8(float x)
     return __int_as_float(max(b, dpp_i<0x141>(b)));
 }
 
-// int8 codes of eight values y = x / s: clamped to [lo, 127] (lo = -127 for m; for sqrt(v)
-// or v, 1 in a non-zero block and 0 in an all-zero one), rounded to nearest even, packed.
-// Clamping before rounding gives the same integer, as both bounds are integers.  Adding
-// 1.5 * 2^23 does the rounding (the sum's ulp is 1) and leaves the integer's two's-
-// complement low byte as the sum's low byte.
-__device__ __forceinline__ u32x2_t pack_codes(const float (&y)[8], const float (&lo)[8])
+// int8 codes of eight values x with the reciprocals r of their scales: x r rounded to nearest
+// even, clamped to [lo, 127] (lo = -127 for m; for sqrt(v) or v, 1 in a non-zero block and 0
+// in an all-zero one), packed.  Adding 1.5 * 2^23 in the product's fma does the rounding (the
+// sum's ulp is 1, and nothing is rounded before it) and leaves the integer's two's-complement
+// low byte as the sum's low byte; the clamp's bounds are integers, so it may follow.
+__device__ __forceinline__ u32x2_t pack_codes(const float (&x)[8], const float (&r)[8], const float (&lo)[8])
 {
+    constexpr float MAGIC = 12582912.0f;
     uint32_t b[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) b[e] = __float_as_uint(__builtin_amdgcn_fmed3f(y[e], lo[e], 127.0f) + 12582912.0f);
-    u32x2_t r;
+    for (int e = 0; e < 8; ++e)
+        b[e] = __float_as_uint(
+            __builtin_amdgcn_fmed3f(__builtin_fmaf(x[e], r[e], MAGIC), MAGIC + lo[e], MAGIC + 127.0f));
+    u32x2_t c;
 #pragma unroll
     for (int k = 0; k < 2; ++k)
-        r[k] = __builtin_amdgcn_perm(b[4 * k + 1], b[4 * k], 0x0c0c0400u) |
+        c[k] = __builtin_amdgcn_perm(b[4 * k + 1], b[4 * k], 0x0c0c0400u) |
                __builtin_amdgcn_perm(b[4 * k + 3], b[4 * k + 2], 0x04000c0cu);
-    return r;
+    return c;
 }
-__device__ __forceinline__ u32x2_t pack_codes(const float (&y)[8], float lo)
+__device__ __forceinline__ u32x2_t pack_codes(const float (&x)[8], float r, float lo)
 {
-    const float l[8] = {lo, lo, lo, lo, lo, lo, lo, lo};
-    return pack_codes(y, l);
+    const float rr[8] = {r, r, r, r, r, r, r, r}, l[8] = {lo, lo, lo, lo, lo, lo, lo, lo};
+    return pack_codes(x, rr, l);
 }
 
 // x / 127 in fp32, correctly rounded for every finite x >= 0: the product with RN(1/127)
@@ -761,13 +764,17 @@ struct EpiI8Row {
         const f32x4_t g0 = *reinterpret_cast<const f32x4_t *>(gr);
         const f32x4_t g1 = *reinterpret_cast<const f32x4_t *>(gr + 4);
         float wo[8], mo[8], vo[8];
+        // the block's scales multiply the codes by way of the recurrence's constants
+        Hyper hk = h;
+        hk.b1 *= sm[i];
+        hk.b2 *= sv[i];
         float am = 0.0f, av = 0.0f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const float g = e < 4 ? g0[e] : g1[e - 4];
             const float w = (e & 1) ? bf_hi(pw[i][e >> 1]) : bf_lo(pw[i][e >> 1]);
             float rv;
-            adamw_elem(g, w, sm[i] * code_at(pm[i], e), sv[i] * code_at(pv[i], e), h, wo[e], mo[e], vo[e], rv);
+            adamw_elem(g, w, code_at(pm[i], e), code_at(pv[i], e), hk, wo[e], mo[e], vo[e], rv);
             am = fmaxf(am, fabsf(mo[e]));
             av = fmaxf(av, vo[e]);
         }
@@ -777,13 +784,7 @@ struct EpiI8Row {
         const float scm = div127(am), scv = div127(av);
         const float rcm = scm > 0.0f ? __builtin_amdgcn_rcpf(scm) : 0.0f;
         const float rcv = scv > 0.0f ? __builtin_amdgcn_rcpf(scv) : 0.0f;
-        float ym[8], yv[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            ym[e] = mo[e] * rcm;
-            yv[e] = vo[e] * rcv;
-        }
-        const u32x2_t cm = pack_codes(ym, -127.0f), cv = pack_codes(yv, rcv > 0.0f ? 1.0f : 0.0f);
+        const u32x2_t cm = pack_codes(mo, rcm, -127.0f), cv = pack_codes(vo, rcv, rcv > 0.0f ? 1.0f : 0.0f);
         if (ok) {
             const size_t off = (size_t)p * a.d_in + q;
             u32x4_t wn;
@@ -1158,10 +1159,12 @@ struct EpiAdamWI8 {
     __device__ __forceinline__ void state_at(const Args &a, int i, const float *g, int e,
                                              float &w1, float &m1, float &v1, float &rv1) const
     {
-        const float m0 = sm[e] * code_at(pm[i], e);
-        const float r0 = sv[e] * code_at(pv[i], e);
+        const float qv = code_at(pv[i], e);
         const float w0 = (e & 1) ? bf_hi(pw[i][e >> 1]) : bf_lo(pw[i][e >> 1]);
-        adamw_elem(g[e], w0, m0, r0 * r0, a.h, w1, m1, v1, rv1);
+        Hyper hk = a.h;
+        hk.b1 = sm[e];
+        hk.b2 = sv[e];
+        adamw_elem(g[e], w0, code_at(pm[i], e), qv * qv, hk, w1, m1, v1, rv1);   // qv * qv is exact
     }
 
     // Contains one LDS barrier (the cross-wave absmax), which every wave of the
@@ -1174,6 +1177,12 @@ struct EpiAdamWI8 {
         float am[8], av[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) am[e] = av[e] = 0.0f;
+        // the scales multiply the codes by way of the recurrence's constants: b1 s_m, b2 s_v^2
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            sm[e] *= a.h.b1;
+            sv[e] *= a.h.b2 * sv[e];
+        }
 
         // pass 1: weight update (from the unquantised fp32 state) and block absmax
 #pragma unroll
@@ -1267,21 +1276,19 @@ struct EpiAdamWI8 {
             const f32x4_t g0 = *reinterpret_cast<const f32x4_t *>(gr);
             const f32x4_t g1 = *reinterpret_cast<const f32x4_t *>(gr + 4);
             const float g[8] = {g0[0], g0[1], g0[2], g0[3], g1[0], g1[1], g1[2], g1[3]};
-            uint32_t cm[2] = {0u, 0u}, cv[2] = {0u, 0u};
+            float mo[8], ro[8], lom[8], lov[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                float w1, m1, v1, rv1;
-                state_at(a, i, g, e, w1, m1, v1, rv1);
-                const float qm = fminf(fmaxf(__builtin_rintf(m1 * rcm[e]), -127.0f), 127.0f);
-                float qv = fminf(fmaxf(__builtin_rintf(rv1 * rcv[e]), 1.0f), 127.0f);
-                if (!(rcv[e] > 0.0f)) qv = 0.0f;
-                cm[e >> 2] |= ((uint32_t)(int32_t)qm & 0xFFu) << (8 * (e & 3));
-                cv[e >> 2] |= ((uint32_t)(int32_t)qv & 0xFFu) << (8 * (e & 3));
+                float w1, v1;
+                state_at(a, i, g, e, w1, mo[e], v1, ro[e]);
+                lom[e] = -127.0f;
+                lov[e] = rcv[e] > 0.0f ? 1.0f : 0.0f;
             }
+            const u32x2_t cm = pack_codes(mo, rcm, lom), cv = pack_codes(ro, rcv, lov);
             if (qok && p < a.d_out) {
                 const size_t off = (size_t)p * a.d_in + q;
-                st_nt<u32x2_t>(static_cast<int8_t *>(a.m) + off, u32x2_t{cm[0], cm[1]});
-                st_nt<u32x2_t>(static_cast<int8_t *>(a.v) + off, u32x2_t{cv[0], cv[1]});
+                st_nt<u32x2_t>(static_cast<int8_t *>(a.m) + off, cm);
+                st_nt<u32x2_t>(static_cast<int8_t *>(a.v) + off, cv);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -1775,6 +1782,16 @@ struct StreamI8 {
         else load_scales(a, p0, q0, s);
     }
 
+    // The scales multiply the codes by way of the recurrence's constants: b1 s_m, b2 s_v^2.
+    __device__ __forceinline__ void fold_scales(const Hyper &h)
+    {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            sm[e] *= h.b1;
+            sv[e] *= h.b2 * sv[e];
+        }
+    }
+
     // Wait once for the slot's loads (issued a period earlier, so long done), then hide
     // the registers from the compiler's wait tracking: what follows does not wait for the
     // stores of the previous tile.
@@ -1820,10 +1837,12 @@ struct StreamI8 {
     __device__ __forceinline__ void state_at(const Hyper &h, int i, float g, int e, float &w1, float &m1,
                                              float &v1, float &rv1) const
     {
-        const float m0 = sm[e] * EpiAdamWI8<BP_I8, BQ_I8>::code_at(cm[i], e);
-        const float r0 = sv[e] * EpiAdamWI8<BP_I8, BQ_I8>::code_at(cv[i], e);
+        const float qm = EpiAdamWI8<BP_I8, BQ_I8>::code_at(cm[i], e), qv = EpiAdamWI8<BP_I8, BQ_I8>::code_at(cv[i], e);
         const float w0 = (e & 1) ? bf_hi(w[i][e >> 1]) : bf_lo(w[i][e >> 1]);
-        adamw_elem(g, w0, m0, r0 * r0, h, w1, m1, v1, rv1);
+        Hyper hk = h;
+        hk.b1 = sm[e];
+        hk.b2 = sv[e];
+        adamw_elem(g, w0, qm, qv * qv, hk, w1, m1, v1, rv1);   // qv * qv is exact
     }
 
     // Pass 1, row I of tile (p0, q0), from the unquantised fp32 state: W' is stored, m'
@@ -1941,14 +1960,11 @@ struct StreamI8 {
     __device__ __forceinline__ void pass2(const Args &a, int p0, int q0, int s, const float *Gs)
     {
         const int p = p0 + I * M::RPP + s / M::LPR, q = q0 + (s % M::LPR) * 8;
-        float ym[8], yv[8];
-        g_row<I>(Gs, s, ym);
+        float mo[8], lom[8];
+        g_row<I>(Gs, s, mo);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            ym[e] *= rcm[e];
-            yv[e] = rv[I][e] * rcv[e];
-        }
-        const u32x2_t qm = pack_codes(ym, -127.0f), qv = pack_codes(yv, lov);
+        for (int e = 0; e < 8; ++e) lom[e] = -127.0f;
+        const u32x2_t qm = pack_codes(mo, rcm, lom), qv = pack_codes(rv[I], rcv, lov);
         if (p < a.d_out && q < a.d_in) {
             const size_t off = (size_t)p * a.d_in + q;
             st_nt<u32x2_t>(static_cast<int8_t *>(a.m) + off, qm);
@@ -1993,6 +2009,7 @@ struct StreamI8 {
         const int half = nb / 2;
         int done = 0;
         reset();
+        fold_scales(a.h);
         p1_all(a, p0, q0, s, Gs, an, pn, qn, refill, half, done, red);
         scales(a, p0, q0, s, red);
         lds_barrier();                                       // B
