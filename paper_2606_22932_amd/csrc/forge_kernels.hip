@@ -54,8 +54,9 @@ constexpr int I8_BLOCK = 256;   // rows of d_out sharing one int8 scale
 // block tall so that the block absmax closes inside the workgroup.
 constexpr int BP_F = 128, BQ_F = 128;
 constexpr int BP_I8 = 256, BQ_I8 = 64;
-// Tiles of the long-loop kernel.
+// Tiles of the long-loop kernels (int8: one scale block tall).
 constexpr int BP_W = 128, BQ_W = 256;
+constexpr int BP_WI8 = 256, BQ_WI8 = 128;
 
 // ------------------------------------------------------------------------ small helpers
 
@@ -2096,6 +2097,232 @@ __global__ void __launch_bounds__(NT_I8P, NT_I8P / 256) pipelined_i8_kernel(Grou
     }
 }
 
+// ------------------------------------------------ int8 moments: long token loops
+//
+// The column layout in the manner of wide_kernel: 256 x 128 tiles, one scale block tall, four
+// waves of 64 x 128, two workgroups per CU.  The block's new scales need the absmax of every
+// m' and sqrt(v') of the tile before any is quantised, and those are twice what the registers
+// hold, so two passes compute them from the same numbers, G (kept in the accumulators), the
+// codes and the old scales: the first updates W and takes the absmax, the second quantises.
+// The second reads the codes again, from the caches they came through a few microseconds
+// before.  Bit-identical to pipelined_i8_kernel.
+struct WideI8 {
+    using M = EpiMap<32, BQ_WI8, 64>;
+    static constexpr int AH = 4;                         // passes in flight
+    static constexpr int RED = 4 * BQ_WI8;               // absmax partials of m, then of sqrt(v): [wave][column]
+    u32x4_t pw[AH];
+    u32x2_t pm[AH], pv[AH];
+    float km[8], kv[8];                                  // b1 s_m and b2 s_v^2 of this lane's columns
+    float am[8], av[8];                                  // absmax so far; then the new scales' reciprocals
+
+    // State of row pass i of the wave's sixteen (rows p + 4 i ..) into slot i % AH.
+    __device__ __forceinline__ void load(int i, const Args &a, int p, int q0, int lane, bool w)
+    {
+        const int row = p + i * M::RPP + lane / M::LPR, q = q0 + (lane % M::LPR) * 8;
+        const uint64_t n = (uint64_t)a.d_out * (uint64_t)a.d_in;
+        const uint32_t off = elem_off(row, q, a.d_out, a.d_in, 1);
+        const int k = i % AH;
+        if (w) pw[k] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_of(a.W, 2ull * n), elem_off(row, q, a.d_out, a.d_in, 2), 0, 2);
+        // plain loads: the codes are read twice
+        pm[k] = __builtin_amdgcn_raw_buffer_load_b64(rsrc_of(a.m, n), off, 0, 0);
+        pv[k] = __builtin_amdgcn_raw_buffer_load_b64(rsrc_of(a.v, n), off, 0, 0);
+    }
+
+    __device__ __forceinline__ void load_scales(const Args &a, int p0, int q0, int lane)
+    {
+        const int q = q0 + (lane % M::LPR) * 8, blk = p0 / I8_BLOCK, nblk = (a.d_out + I8_BLOCK - 1) / I8_BLOCK;
+        const uint64_t n = 4ull * (uint64_t)nblk * (uint64_t)a.d_in;
+        const uint32_t off = elem_off(blk, q, nblk, a.d_in, 4), off4 = off == OOR_OFFSET ? off : off + 16u;
+        const __amdgpu_buffer_rsrc_t rm = rsrc_of(a.ms, n), rv = rsrc_of(a.vs, n);
+        const f32x4_t s0 = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rm, off, 0, 0));
+        const f32x4_t s1 = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rm, off4, 0, 0));
+        const f32x4_t t0 = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rv, off, 0, 0));
+        const f32x4_t t1 = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rv, off4, 0, 0));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            km[e] = s0[e]; km[e + 4] = s1[e];
+            kv[e] = t0[e]; kv[e + 4] = t1[e];
+        }
+    }
+
+    __device__ __forceinline__ void begin(const Hyper &h)
+    {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            km[e] *= h.b1;
+            kv[e] *= h.b2 * kv[e];
+            am[e] = av[e] = 0.0f;
+        }
+    }
+
+    // m', sqrt(v') (and W') of the eight elements of row pass i, whose state is in its slot.
+    __device__ __forceinline__ void step(int i, const Hyper &h, int lane, const float *Gs, float (&wo)[8], float (&mo)[8],
+                                         float (&ro)[8]) const
+    {
+        const float *gr = Gs + ((i & 7) * M::RPP + lane / M::LPR) * M::GP + (lane % M::LPR) * 8;
+        const f32x4_t g0 = *reinterpret_cast<const f32x4_t *>(gr);
+        const f32x4_t g1 = *reinterpret_cast<const f32x4_t *>(gr + 4);
+        const int k = i % AH;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            using C = EpiAdamWI8<BP_I8, BQ_I8>;
+            const float g = e < 4 ? g0[e] : g1[e - 4];
+            const float w = (e & 1) ? bf_hi(pw[k][e >> 1]) : bf_lo(pw[k][e >> 1]);
+            const float qv = C::code_at(pv[k], e);
+            Hyper hk = h;
+            hk.b1 = km[e];
+            hk.b2 = kv[e];
+            float v1;
+            adamw_elem(g, w, C::code_at(pm[k], e), qv * qv, hk, wo[e], mo[e], v1, ro[e]);   // qv * qv is exact
+        }
+    }
+
+    __device__ __forceinline__ void pass1(int i, const Args &a, const Hyper &h, int p, int q0, int lane, const float *Gs)
+    {
+        const int row = p + i * M::RPP + lane / M::LPR, q = q0 + (lane % M::LPR) * 8;
+        float wo[8], mo[8], ro[8];
+        step(i, h, lane, Gs, wo, mo, ro);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            am[e] = fmaxf(am[e], fabsf(mo[e]));
+            av[e] = fmaxf(av[e], ro[e]);
+        }
+        // close the pass: maxima of several passes kept apart would spill
+#pragma unroll
+        for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(am[e]), "+v"(av[e]));
+        if (row < a.d_out && q < a.d_in) {
+            u32x4_t wn;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) wn[k] = pack_bf16(wo[2 * k], wo[2 * k + 1]);
+            st_nt<u32x4_t>(a.W + (size_t)row * a.d_in + q, wn);
+        }
+    }
+
+    // The wave's absmax of its columns (lanes l, l^16, l^32, l^48 hold the same ones) to LDS.
+    __device__ __forceinline__ void partials(int wave, int lane, float *red)
+    {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            int x[2] = {__float_as_int(am[e]), __float_as_int(av[e])};
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const auto h = __builtin_amdgcn_permlane16_swap(x[k], x[k], false, false);
+                x[k] = max((int)h[0], (int)h[1]);
+                const auto w = __builtin_amdgcn_permlane32_swap(x[k], x[k], false, false);
+                x[k] = max((int)w[0], (int)w[1]);
+                if (lane < M::LPR) red[k * RED + wave * BQ_WI8 + lane * 8 + e] = __int_as_float(x[k]);
+            }
+        }
+    }
+
+    // After a barrier: one column's new scale per thread (m by the first BQ threads, sqrt(v) by
+    // the others): stored, and its reciprocal left in LDS.
+    __device__ __forceinline__ void scales(const Args &a, int p0, int q0, int tid, float *red)
+    {
+        const int kind = tid / BQ_WI8, c = tid % BQ_WI8;
+        const float *r = red + kind * RED + c;
+        float x = r[0];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) x = fmaxf(x, r[w * BQ_WI8]);
+        const float sc = x / 127.0f;
+        red[2 * RED + tid] = sc > 0.0f ? __builtin_amdgcn_rcpf(sc) : 0.0f;
+        if (q0 + c < a.d_in) st_nt<float>((kind ? a.vs : a.ms) + (size_t)(p0 / I8_BLOCK) * a.d_in + q0 + c, sc);
+    }
+
+    // After another: the reciprocals of this lane's columns, in place of the maxima.
+    __device__ __forceinline__ void recips(int lane, const float *red)
+    {
+        const float *r = red + 2 * RED + (lane % M::LPR) * 8;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            am[e] = r[e];
+            av[e] = r[BQ_WI8 + e];
+        }
+    }
+
+    __device__ __forceinline__ void pass2(int i, const Args &a, const Hyper &h, int p, int q0, int lane, const float *Gs)
+    {
+        const int row = p + i * M::RPP + lane / M::LPR, q = q0 + (lane % M::LPR) * 8;
+        float wo[8], mo[8], ro[8], lom[8], lov[8];
+        step(i, h, lane, Gs, wo, mo, ro);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            lom[e] = -127.0f;
+            lov[e] = av[e] > 0.0f ? 1.0f : 0.0f;
+        }
+        const u32x2_t cm = pack_codes(mo, am, lom), cv = pack_codes(ro, av, lov);
+        if (row < a.d_out && q < a.d_in) {
+            const size_t off = (size_t)row * a.d_in + q;
+            st_nt<u32x2_t>(static_cast<int8_t *>(a.m) + off, cm);
+            st_nt<u32x2_t>(static_cast<int8_t *>(a.v) + off, cv);
+        }
+    }
+};
+
+__global__ void __launch_bounds__(NROLE, 2) wide_i8_kernel(GroupArgs g)
+{
+    using L = WideLoop<BP_WI8, BQ_WI8>;
+    using EM = WideI8::M;
+    constexpr int AH = WideI8::AH;
+    constexpr int GS = L::NW * EM::GS_BYTES;
+    constexpr int RED_BYTES = (2 * WideI8::RED + 2 * BQ_WI8) * 4;
+    constexpr int MAIN = L::NS * L::STAGE > GS + RED_BYTES ? L::NS * L::STAGE : GS + RED_BYTES;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[MAIN];
+    float *red = reinterpret_cast<float *>(smem + GS);
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float *Gs = reinterpret_cast<float *>(smem + wave * EM::GS_BYTES);
+    for (int b = blockIdx.x; b < g.start[g.n]; b += gridDim.x) {
+        // Hidden from the compiler, which would otherwise keep what it derives from the lane
+        // number for all tiles, in registers that the tile needs.
+        int lane = tid & 63;
+        asm volatile("" : "+v"(lane));
+        const int t = xcd_remap(b, g.start[g.n]);
+        int mi = 0;
+        while (mi + 1 < g.n && t >= g.start[mi + 1]) ++mi;
+        const Args a = g.a[mi];
+        int tp, tq;
+        raster(t - g.start[mi], a.tiles_p, a.tiles_q, a.group_p, tp, tq);
+        const int p0 = tp * L::BP, q0 = tq * L::BQ, p = p0 + wave * 64;
+        const Hyper h = a.h;
+
+        L ml;
+        WideI8 ep;
+        ml.run(a, p0, q0, smem, wave, lane, [&]() {
+            ep.load_scales(a, p0, q0, lane);
+#pragma unroll
+            for (int i = 0; i < AH; ++i) ep.load(i, a, p, q0, lane, true);
+        });
+        lds_barrier();                                   // every wave is done reading the ring
+        ep.begin(h);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            if ((i & 7) == 0) ml.template stage_g<EM::GP>(Gs, i >> 3, lane);
+            ep.pass1(i, a, h, p, q0, lane, Gs);
+            if (i + AH < 16) ep.load(i + AH, a, p, q0, lane, true);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // the second pass starts with the rows that are staged
+#pragma unroll
+        for (int i = 0; i < AH; ++i) ep.load(8 + i, a, p, q0, lane, false);
+        ep.partials(wave, lane, red);
+        lds_barrier();
+        ep.scales(a, p0, q0, tid, red);
+        lds_barrier();
+        ep.recips(lane, red);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int i = (j + 8) & 15, nx = j + AH;
+            if (j == 8) ml.template stage_g<EM::GP>(Gs, 0, lane);
+            ep.pass2(i, a, h, p, q0, lane, Gs);
+            if (nx < 16) ep.load((nx + 8) & 15, a, p, q0, lane, false);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        lds_barrier();                                   // the next tile's chunks overwrite the staged G
+    }
+}
+
 // ------------------------------------------------------------------------ launchers
 
 TileShape tile_shape(int mk)
@@ -2224,6 +2451,17 @@ static int raster_rows_i8(int T)
 // int8 moments in 256-row blocks.
 static hipError_t launch_i8(const Args *a, int n, hipStream_t st)
 {
+    // wide_i8_kernel on 256 x 128 tiles (raster groups of 8 tile rows), where they occupy at
+    // least three quarters of its 2 * CUs workgroups, or half with long token loops.  Against the
+    // kernel below, microseconds: 14336 x 4096 151 : 175 at T = 512, 298 : 411 at T = 2048; 4096 x
+    // 4096 (512 tiles) 36 : 42 at T = 128, 46 : 57 at T = 512; 5000 x 3000 (480) 52 : 64; but
+    // 4096 x 2048 (256) 32 : 31 at T = 512 and 57 : 65 at T = 2048, 2048 x 2048 (128) 29 : 19.
+    const GroupArgs w = group_of(a, n, BP_WI8, BQ_WI8, 8);
+    const int wtiles = w.start[n], slots = 2 * device_cu_count();
+    if (4 * wtiles >= 3 * slots || (2 * wtiles >= slots && a[0].T >= 1024)) {
+        hipLaunchKernelGGL(wide_i8_kernel, dim3(wtiles < slots ? wtiles : slots), dim3(NROLE), 0, st, w);
+        return hipGetLastError();
+    }
     const GroupArgs g = group_of(a, n, BP_I8, BQ_I8, raster_rows_i8(a[0].T));
     const int total = g.start[n];
     if (total == 0) return hipSuccess;
