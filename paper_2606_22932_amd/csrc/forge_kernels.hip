@@ -2386,6 +2386,23 @@ static bool wide_pays(int mk, int epi, int T, int tiles)
     return T >= (w8 || mk == MK_I8R64 || mk == MK_FP8 ? 512 : 1024);
 }
 
+// Raster rows for fp32 state, whose rows of 4 B elements span twice the memory of bf16's: 4, so
+// that an XCD's tiles lie in few, whole rows of the state, or all of them on grids of at most
+// 32 x 32 tiles (and more than 16 high).  Matrices less than 2048 wide keep the shape rule
+// (1024 x 4096 with all rows 18.9 : 17.2).  Against the shape rule at T = 512, microseconds, AdamW and SGD with momentum:
+// 8192 x 8192 291 : 317 and 198 : 201, 8192 x 2048 80 : 87 and 55 : 61, 14336 x 4096 244 : 245,
+// 1024 x 4096 24.1 : 25.4; 4096 x 4096 (all rows) 76 : 80 and 54 : 57 (with 4: 83 and 56).  Long
+// token loops keep the shape rule: their operand slabs want compact tile groups.
+static int raster_rows_f32(const Args *a, int n, int bp, int bq)
+{
+    int rows = 32;
+    for (int i = 0; i < n; ++i) {
+        if (a[i].d_in < 16 * bq) return 0;
+        if (a[i].d_out > 32 * bp || a[i].d_in > 32 * bq || a[i].d_out <= 16 * bp) rows = 4;
+    }
+    return rows;
+}
+
 // The launch of n matrices (all with the same T).
 template <int BP, int BQ, int MK, int EPI>
 static hipError_t launch_group(const Args *a, int n, hipStream_t st)
@@ -2401,7 +2418,10 @@ static hipError_t launch_group(const Args *a, int n, hipStream_t st)
     }
     // int8 row-block state: groups of 8 tile rows (measured on the MLP projections at
     // T = 512: 5 % faster than the shape rule, whose 24-row groups suit bf16 state)
-    const GroupArgs g = group_of(a, n, BP, BQ, MK == MK_I8R64 ? 8 : 0);
+    // fp32 state and short token loops: below.
+    int rows = MK == MK_I8R64 ? 8 : 0;
+    if (MK == MK_F32 && a[0].T < 1024) rows = raster_rows_f32(a, n, BP, BQ);
+    const GroupArgs g = group_of(a, n, BP, BQ, rows);
     if (g.start[n] == 0) return hipSuccess;
     // Prefetch depth by launch length (AdamW on bf16 state): a launch of at least 8 waves of
     // resident tiles, or with a long token loop (T >= 1024), loads all eight
