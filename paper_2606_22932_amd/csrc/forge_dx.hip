@@ -12,8 +12,7 @@
 //
 // One workgroup owns an output tile dX[t0 : t0+BT, q0 : q0+BQ] held in fp32 registers: four
 // waves for 64- and 128-row tiles of 128 columns, eight waves (two per SIMD, each holding
-// 128 x 64 outputs) for 256 x 256 tiles, which halve the LDS fragment reads per flop and
-// are chosen once they alone fill the compute units.  MFMA (v_mfma_f32_32x32x16_bf16) operand A is W^T (M = q along d_in, K = p
+// 128 x 64 outputs) for 256 x 256 tiles, which halve the LDS fragment reads per flop.  MFMA (v_mfma_f32_32x32x16_bf16) operand A is W^T (M = q along d_in, K = p
 // along d_out), operand B is dY^T (K = p, N = t); each lane of a 32x32 result holds four
 // consecutive q of one token row, which is the order the tile is staged in for its stores.
 #include "forge_device.h"
@@ -374,17 +373,27 @@ __global__ void __launch_bounds__(64 * NW, (BK == 64 || NW > 4) ? 1 : 2) dx_kern
     tile.store(g, t0, q0, smem, wave, lane, tid);
 }
 
-// Token rows per tile: 256 (256 x 256 tiles, 2x4 waves of 128x64) once those alone cover
-// every compute unit; else 128 (2x2 waves of 64x64) once the 128x128 tiles do; else 64 (4x1
-// waves of 32 columns x 64 rows), which doubles the tile count for the short token axes of
-// fine-tuning-sized batches.  Every choice sums over K in the same order: dX is the same
-// bits whichever tile computes it.
+// Token rows per tile, by the rounds of tiles that the chip needs.  Cost of a tile per row of K,
+// in 10 ps (measured on d_in 776-14336 at T = 64-4096): 64 x 128 tiles, one per CU, 62 a round;
+// 128 x 128 tiles 114 with one per CU, 177 with two; 256 x 256 tiles, one per CU, 237 in a round
+// that leaves CUs idle, 293 in a full one (the clock drops).  Against the largest tile whose
+// grid covers the CUs, microseconds: d_in = 14336, d_out = 4096 at T = 1024 118 : 166, at
+// T = 256 57 : 65; 8192 x 8192 at T = 1536 201 : 264, at T = 333 90 : 103; 4160 x 4160 at T = 512
+// 47 : 52, at T = 4096 182 : 213; 4096 x 4096 at T = 777 48 : 54.  Every choice sums over K in the
+// same order: dX is the same bits whichever tile computes it.
 static int dx_rows(int T, int d_in)
 {
     if (FORGE_DX_BT) return FORGE_DX_BT;
-    if ((long)((T + 255) / 256) * (long)((d_in + 255) / 256) >= (long)device_cu_count()) return 256;
-    const long t128 = (long)((T + 127) / 128) * (long)((d_in + DX_BQ - 1) / DX_BQ);
-    return t128 >= (long)device_cu_count() ? 128 : 64;
+    const long cus = device_cu_count();
+    auto tiles = [&](long bt, long bq) { return (T + bt - 1) / bt * ((d_in + bq - 1) / bq); };
+    const long n64 = tiles(64, DX_BQ), n128 = tiles(128, DX_BQ), n256 = tiles(256, 256);
+    const long c64 = (n64 + cus - 1) / cus * 62;
+    // a remainder behind full rounds costs less than a round only if it is small
+    const long f128 = n128 / (2 * cus), r128 = n128 % (2 * cus);
+    const long c128 = f128 * 177 + (r128 == 0 ? 0 : r128 <= (f128 ? cus / 2 : cus) ? 114 : 177);
+    const long c256 = n256 / cus * 293 + (n256 % cus == 0 ? 0 : 237);
+    if (c256 <= c128 && c256 <= c64) return 256;
+    return c128 <= c64 ? 128 : 64;
 }
 
 hipError_t launch_dx(const DxSeg *s, int n, uint16_t *dX, int T, int d_in, hipStream_t st)
