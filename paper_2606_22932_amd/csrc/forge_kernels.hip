@@ -265,7 +265,10 @@ struct Mainloop {
     }
 
     // The token loop of a tile started with begin(); executes exactly nch(T) workgroup
-    // barriers (one per chunk).
+    // barriers (one per chunk).  Behind a chunk's barrier every wave is done with the chunk
+    // before it, whose stage is refilled at once, before the products: the loop waits on this
+    // DMA (bf16 state at T = 512, with the refill behind the products: gate and up, 28672 x
+    // 4096, 279.6 against 275.5 us, 128256 x 4096 1206 against 1187 us).
     __device__ __forceinline__ void body(const Args &a, unsigned char *lds, int wave)
     {
         const int nch = (a.T + TK - 1) / TK;
@@ -273,10 +276,10 @@ struct Mainloop {
         for (int c = 0; c < nch; ++c) {
             const int younger = min(NS - 2, nch - 1 - c);
             wait_chunk(younger);
+            if (c + NS - 1 < nch) issue(a, lds + ((c + NS - 1) % NS) * STAGE_BYTES, c + NS - 1, wave);
 #pragma unroll
             for (int h = 0; h < TK / 32; ++h)    // 32 tokens per compute(); X and Y rows of equal length
                 compute(lds_base + (uint32_t)((c % NS) * STAGE_BYTES + h * 32 * XROWB));
-            if (c + NS - 1 < nch) issue(a, lds + ((c + NS - 1) % NS) * STAGE_BYTES, c + NS - 1, wave);
         }
     }
 
