@@ -264,11 +264,19 @@ struct Mainloop {
             if (c < nch) issue(a, lds + c * STAGE_BYTES, c, wave);
     }
 
+    __device__ __forceinline__ void refill(const Args &a, unsigned char *lds, int c, int nch, int wave)
+    {
+        if (c + NS - 1 < nch) issue(a, lds + ((c + NS - 1) % NS) * STAGE_BYTES, c + NS - 1, wave);
+    }
+
     // The token loop of a tile started with begin(); executes exactly nch(T) workgroup
     // barriers (one per chunk).  Behind a chunk's barrier every wave is done with the chunk
-    // before it, whose stage is refilled at once, before the products: the loop waits on this
+    // before it, whose stage EARLY refills at once, before the products: the loop waits on this
     // DMA (bf16 state at T = 512, with the refill behind the products: gate and up, 28672 x
-    // 4096, 279.6 against 275.5 us, 128256 x 4096 1206 against 1187 us).
+    // 4096, 279.6 against 275.5 us, 128256 x 4096 1206 against 1187 us; int8 columns, 552 x 6216
+    // at T = 2048, 67.0 against 65.8 us).  Short launches of bf16 state measured the other way
+    // (launch_group).
+    template <bool EARLY>
     __device__ __forceinline__ void body(const Args &a, unsigned char *lds, int wave)
     {
         const int nch = (a.T + TK - 1) / TK;
@@ -276,10 +284,11 @@ struct Mainloop {
         for (int c = 0; c < nch; ++c) {
             const int younger = min(NS - 2, nch - 1 - c);
             wait_chunk(younger);
-            if (c + NS - 1 < nch) issue(a, lds + ((c + NS - 1) % NS) * STAGE_BYTES, c + NS - 1, wave);
+            if constexpr (EARLY) refill(a, lds, c, nch, wave);
 #pragma unroll
             for (int h = 0; h < TK / 32; ++h)    // 32 tokens per compute(); X and Y rows of equal length
                 compute(lds_base + (uint32_t)((c % NS) * STAGE_BYTES + h * 32 * XROWB));
+            if constexpr (!EARLY) refill(a, lds, c, nch, wave);
         }
     }
 
@@ -289,12 +298,13 @@ struct Mainloop {
     // of them in the CU's vector memory path.  Without state to load (the store-G
     // epilogue) it only delays the mainloop: 1.5 % on the 4096 x 4096 store-G GEMM at
     // T = 4096.
+    template <bool EARLY>
     __device__ __forceinline__ void run(const Args &a, int p0, int q0, unsigned char *lds, int wave,
                                         int lane, bool lead)
     {
         begin(a, p0, q0, lds, wave, lane);
         if (lead) lds_barrier();
-        body(a, lds, wave);
+        body<EARLY>(a, lds, wave);
         lds_barrier();   // every wave is done reading the stages, which G reuses
     }
 
@@ -1328,7 +1338,7 @@ __device__ __forceinline__ void epi_store_g(const Args &a, int p0, int q0, int s
 
 // At most 128 VGPRs (four waves per SIMD): two 512-thread workgroups per CU, one math and
 // one stream wave of each on every SIMD.  At 129-136 registers only one would fit.
-template <int BP, int BQ, int MK, int EPI, int AH = 0>
+template <int BP, int BQ, int MK, int EPI, int AH = 0, bool EARLY = true>
 __global__ void __launch_bounds__(NT, 4) fused_kernel(GroupArgs g)
 {
     static_assert(MK != MK_I8, "int8 moments run in pipelined_i8_kernel");
@@ -1361,7 +1371,7 @@ __global__ void __launch_bounds__(NT, 4) fused_kernel(GroupArgs g)
     const int p0 = tp * BP, q0 = tq * BQ;
     if (wave < 4) {
         ML ml;
-        ml.run(a, p0, q0, smem, wave, lane, LEAD);
+        ml.template run<EARLY>(a, p0, q0, smem, wave, lane, LEAD);
         ml.template stage_g<EM::GP>(Gs, wave, lane);
         lds_barrier();
         if constexpr (Q8) lds_barrier();
@@ -2060,7 +2070,7 @@ __global__ void __launch_bounds__(NT_I8P, NT_I8P / 256) pipelined_i8_kernel(Grou
         locate(0, mi, p0, q0);
         ml.begin(g.a[mi], p0, q0, ring, wave, lane);
         for (int k = 0; k < K; ++k) {
-            ml.body(g.a[mi], ring, wave);
+            ml.template body<true>(g.a[mi], ring, wave);
             for (int c = nch; c < nb; ++c) lds_barrier();
             lds_barrier();                                   // H1: the stream waves hold G(k-1)
             ml.template stage_g<EM::GP>(Gs, wave, lane);
@@ -2354,6 +2364,14 @@ static Args with_grid(Args a, int bp, int bq, int &ntiles, int group_p = 0)
     return a;
 }
 
+// Tiles of n matrices in bp x bq tiles.
+static int count_tiles(const Args *a, int n, int bp, int bq)
+{
+    int t = 0;
+    for (int i = 0; i < n; ++i) t += ((a[i].d_out + bp - 1) / bp) * ((a[i].d_in + bq - 1) / bq);
+    return t;
+}
+
 // Tile grids of n matrices in bp x bq tiles (raster groups of group_p tile rows, 0: by shape)
 // and the prefix sums of their tile counts.
 static GroupArgs group_of(const Args *a, int n, int bp, int bq, int group_p)
@@ -2411,10 +2429,10 @@ template <int BP, int BQ, int MK, int EPI>
 static hipError_t launch_group(const Args *a, int n, hipStream_t st)
 {
     if constexpr (EPI != EPI_STORE_BF16 && EPI != EPI_STORE_F32) {
-        // raster groups of 8 tile rows: against 4, 1-8 % faster on 8192 x 8192, even elsewhere
-        const GroupArgs w = group_of(a, n, BP_W, BQ_W, 8);
-        const int tiles = w.start[n], slots = 2 * device_cu_count();
+        const int tiles = count_tiles(a, n, BP_W, BQ_W), slots = 2 * device_cu_count();
         if (wide_pays(MK, EPI, a[0].T, tiles)) {
+            // raster groups of 8 tile rows: against 4, 1-8 % faster on 8192 x 8192, even elsewhere
+            const GroupArgs w = group_of(a, n, BP_W, BQ_W, 8);
             hipLaunchKernelGGL((wide_kernel<MK, EPI>), dim3(tiles < slots ? tiles : slots), dim3(NROLE), 0, st, w);
             return hipGetLastError();
         }
@@ -2436,6 +2454,15 @@ static hipError_t launch_group(const Args *a, int n, hipStream_t st)
     if constexpr (MK == MK_BF16 && EPI == EPI_ADAMW)
         if (g.start[n] >= 8 * 2 * device_cu_count() || a[0].T >= 1024) {
             hipLaunchKernelGGL((fused_kernel<BP, BQ, MK, EPI, 8>), dim3(g.start[n]), dim3(NT), 0, st, g);
+            return hipGetLastError();
+        }
+    // Launches of less than four waves of resident tiles refill the operand ring behind a chunk's
+    // products (Mainloop::body).  Behind against before, bf16 AdamW at T = 512, microseconds:
+    // 4096 x 4096 (2 waves) 48.9 : 49.2, dX and the step of q, k and v (3) 112.5 : 112.9; of
+    // 4096 x 14336 (7) 243.6 : 241.4.
+    if constexpr (MK == MK_BF16 && EPI == EPI_ADAMW)
+        if (g.start[n] < 4 * 2 * device_cu_count()) {
+            hipLaunchKernelGGL((fused_kernel<BP, BQ, MK, EPI, 0, false>), dim3(g.start[n]), dim3(NT), 0, st, g);
             return hipGetLastError();
         }
     hipLaunchKernelGGL((fused_kernel<BP, BQ, MK, EPI>), dim3(g.start[n]), dim3(NT), 0, st, g);
@@ -2479,9 +2506,9 @@ static hipError_t launch_i8(const Args *a, int n, hipStream_t st)
     // kernel below, microseconds: 14336 x 4096 151 : 175 at T = 512, 298 : 411 at T = 2048; 4096 x
     // 4096 (512 tiles) 36 : 42 at T = 128, 46 : 57 at T = 512; 5000 x 3000 (480) 52 : 64; but
     // 4096 x 2048 (256) 32 : 31 at T = 512 and 57 : 65 at T = 2048, 2048 x 2048 (128) 29 : 19.
-    const GroupArgs w = group_of(a, n, BP_WI8, BQ_WI8, 8);
-    const int wtiles = w.start[n], slots = 2 * device_cu_count();
+    const int wtiles = count_tiles(a, n, BP_WI8, BQ_WI8), slots = 2 * device_cu_count();
     if (4 * wtiles >= 3 * slots || (2 * wtiles >= slots && a[0].T >= 1024)) {
+        const GroupArgs w = group_of(a, n, BP_WI8, BQ_WI8, 8);
         hipLaunchKernelGGL(wide_i8_kernel, dim3(wtiles < slots ? wtiles : slots), dim3(NROLE), 0, st, w);
         return hipGetLastError();
     }

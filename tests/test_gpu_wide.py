@@ -136,3 +136,23 @@ def test_long_loop_group_equals_single_steps_bitwise():
     torch.cuda.synchronize()
     for x, y in zip(mats, alone):
         assert all(torch.equal(s, t) for s, t in zip(x[2:], y[2:]))
+
+
+@pytest.mark.parametrize("T", [33, 97, 224])
+def test_refill_order_is_bitwise_neutral(T):
+    """Four waves of resident tiles (on 256 CUs 2048 of 128 x 128; here 65 x 33) and up refill the
+    operand ring before a chunk's products, shorter launches (the slices) behind them: fewer chunks
+    than the ring has stages, one more, and a ring that goes around."""
+    print("case", T, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(14)
+    X, dY = _gauss((T, D_IN), 1.0, gen), _gauss((T, D_OUT), 1e-3, gen)
+    whole = _state("bf16", D_OUT, gen)
+    parts = {r0: {k: t[r0:r0 + SLICE].clone() for k, t in whole.items()} for r0 in range(0, D_OUT, SLICE)}
+    _step("bf16", X, dY, whole)
+    for r0, s in parts.items():
+        _step("bf16", X, dY[:, r0:r0 + SLICE].contiguous(), s)
+    torch.cuda.synchronize()
+    for r0, s in parts.items():
+        for k, t in s.items():
+            assert torch.equal(whole[k][r0:r0 + SLICE], t), (k, r0)
