@@ -388,7 +388,7 @@ forge_status forge_query_tile(int64_t T, int64_t d_in, int64_t d_out, int32_t md
 {
     if (check_dtype_moment(md) != FORGE_OK) return FORGE_ERR_INVALID_DTYPE;
     if (T < 0 || d_in < 0 || d_out < 0) return FORGE_ERR_INVALID_SHAPE;
-    const forge_impl::TileShape t = forge_impl::tile_shape(md);   // one tile per moment kind, any shape
+    const forge_impl::TileShape t = forge_impl::tile_shape(md, T, d_in, d_out);
     if (rows) *rows = t.rows;
     if (cols) *cols = t.cols;
     if (tokens) *tokens = t.tokens;

@@ -88,8 +88,8 @@ enum EpiKind {
 
 struct TileShape { int rows, cols, tokens; };
 
-// Tile geometry used for a moment kind (fused step and stand-alone optimizer alike).
-TileShape tile_shape(int moment_kind);
+// Tile geometry of launch_fused on one matrix (sizes >= 0): the launchers' own choice.
+TileShape tile_shape(int moment_kind, int64_t T, int64_t d_in, int64_t d_out);
 
 // Launchers; they return the hipError_t of the launch.
 hipError_t launch_fused(const Args &a, int moment_kind, hipStream_t stream);

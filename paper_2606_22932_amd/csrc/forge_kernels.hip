@@ -18,6 +18,7 @@
 // of a materialised G into LDS and runs the same epilogue code.
 #include "forge_device.h"
 
+#include <algorithm>
 #include <mutex>
 
 namespace forge_impl {
@@ -2338,12 +2339,6 @@ __global__ void __launch_bounds__(NROLE, 2) wide_i8_kernel(GroupArgs g)
 
 // ------------------------------------------------------------------------ launchers
 
-TileShape tile_shape(int mk)
-{
-    if (mk == MK_I8) return TileShape{BP_I8, BQ_I8, 32};
-    return TileShape{BP_F, BQ_F, TK128};
-}
-
 // Tile rows per raster group, by the shape of the tile grid (measured on the Llama-3.1-8B
 // shapes at T = 512): matrices wider than tall walk 24 rows at a time, very tall ones 8,
 // the rest 16.  The 64 tiles resident on an XCD then span a few hundred KB of operand
@@ -2364,12 +2359,17 @@ static Args with_grid(Args a, int bp, int bq, int &ntiles, int group_p = 0)
     return a;
 }
 
-// Tiles of n matrices in bp x bq tiles.
+// Tiles of one matrix, and of n matrices, in bp x bq tiles.
+static int64_t count_tiles(int64_t d_in, int64_t d_out, int bp, int bq)
+{
+    return (d_out / bp + (d_out % bp != 0)) * (d_in / bq + (d_in % bq != 0));
+}
+
 static int count_tiles(const Args *a, int n, int bp, int bq)
 {
-    int t = 0;
-    for (int i = 0; i < n; ++i) t += ((a[i].d_out + bp - 1) / bp) * ((a[i].d_in + bq - 1) / bq);
-    return t;
+    int64_t t = 0;
+    for (int i = 0; i < n; ++i) t += count_tiles(a[i].d_in, a[i].d_out, bp, bq);
+    return static_cast<int>(t);
 }
 
 // Tile grids of n matrices in bp x bq tiles (raster groups of group_p tile rows, 0: by shape)
@@ -2398,7 +2398,7 @@ static GroupArgs group_of(const Args *a, int n, int bp, int bq, int group_p)
 // fp32 state, but with 8-bit state, whose epilogue is short beside the loop, 1.00-1.12.  fp8
 // weights and moments gain from one tile per workgroup and T = 256 on (1.01-1.08).  With fewer
 // tiles the smaller tiles fill the chip better (2048 x 4096: 0.75-0.95).
-static bool wide_pays(int mk, int epi, int T, int tiles)
+static bool wide_pays(int mk, int epi, int64_t T, int64_t tiles)
 {
     const int slots = 2 * device_cu_count();
     const bool w8 = epi == EPI_ADAMW_WFP8;
@@ -2498,16 +2498,38 @@ static int raster_rows_i8(int T)
     return g;
 }
 
+// Whether a launch of `tiles` 256 x 128 tiles with T tokens runs in wide_i8_kernel: where they
+// occupy at least three quarters of its 2 * CUs workgroups, or half with long token loops.
+// Against pipelined_i8_kernel, microseconds: 14336 x 4096 151 : 175 at T = 512, 298 : 411 at
+// T = 2048; 4096 x 4096 (512 tiles) 36 : 42 at T = 128, 46 : 57 at T = 512; 5000 x 3000 (480)
+// 52 : 64; but 4096 x 2048 (256) 32 : 31 at T = 512 and 57 : 65 at T = 2048, 2048 x 2048 (128)
+// 29 : 19.
+static bool wide_i8_pays(int64_t T, int64_t tiles)
+{
+    const int slots = 2 * device_cu_count();
+    return tiles >= slots - slots / 4 || (tiles >= slots / 2 && T >= 1024);
+}
+
+TileShape tile_shape(int mk, int64_t T, int64_t d_in, int64_t d_out)
+{
+    d_in = std::min<int64_t>(d_in, INT32_MAX);   // larger sizes are refused; their products would not fit
+    d_out = std::min<int64_t>(d_out, INT32_MAX);
+    if (mk == MK_I8) {
+        if (wide_i8_pays(T, count_tiles(d_in, d_out, BP_WI8, BQ_WI8)))
+            return TileShape{BP_WI8, BQ_WI8, WideLoop<BP_WI8, BQ_WI8>::TK};
+        return TileShape{BP_I8, BQ_I8, 32};
+    }
+    if (wide_pays(mk, EPI_ADAMW, T, count_tiles(d_in, d_out, BP_W, BQ_W)))
+        return TileShape{BP_W, BQ_W, WideLoop<BP_W, BQ_W>::TK};
+    return TileShape{BP_F, BQ_F, TK128};
+}
+
 // int8 moments in 256-row blocks.
 static hipError_t launch_i8(const Args *a, int n, hipStream_t st)
 {
-    // wide_i8_kernel on 256 x 128 tiles (raster groups of 8 tile rows), where they occupy at
-    // least three quarters of its 2 * CUs workgroups, or half with long token loops.  Against the
-    // kernel below, microseconds: 14336 x 4096 151 : 175 at T = 512, 298 : 411 at T = 2048; 4096 x
-    // 4096 (512 tiles) 36 : 42 at T = 128, 46 : 57 at T = 512; 5000 x 3000 (480) 52 : 64; but
-    // 4096 x 2048 (256) 32 : 31 at T = 512 and 57 : 65 at T = 2048, 2048 x 2048 (128) 29 : 19.
     const int wtiles = count_tiles(a, n, BP_WI8, BQ_WI8), slots = 2 * device_cu_count();
-    if (4 * wtiles >= 3 * slots || (2 * wtiles >= slots && a[0].T >= 1024)) {
+    if (wide_i8_pays(a[0].T, wtiles)) {
+        // raster groups of 8 tile rows
         const GroupArgs w = group_of(a, n, BP_WI8, BQ_WI8, 8);
         hipLaunchKernelGGL(wide_i8_kernel, dim3(wtiles < slots ? wtiles : slots), dim3(NROLE), 0, st, w);
         return hipGetLastError();

@@ -15,7 +15,7 @@ namespace forge_impl {
     std::abort();
 }
 
-TileShape tile_shape(int) { unreachable("tile_shape"); }
+TileShape tile_shape(int, int64_t, int64_t, int64_t) { unreachable("tile_shape"); }
 hipError_t launch_fused(const Args &, int, hipStream_t) { unreachable("launch_fused"); }
 hipError_t launch_fused_group(const Args *, int, int, hipStream_t) { unreachable("launch_fused_group"); }
 hipError_t launch_fused_rule(const Args *, int, int, int, hipStream_t) { unreachable("launch_fused_rule"); }

@@ -9,6 +9,7 @@ import json
 import os
 
 import pytest
+import torch
 
 from paper_2606_22932_amd import accounting, forge
 
@@ -62,7 +63,7 @@ def test_status_strings():
 
 def test_query_tile():
     assert forge.forge_query_tile(512, 4096, 4096, BF16) == (128, 128, 32)
-    assert forge.forge_query_tile(4096, 4096, 4096, BF16) == (128, 128, 32)   # one tile at every T
+    assert forge.forge_query_tile(4096, 4096, 4096, BF16) == (128, 128, 32)   # too few 128 x 256 tiles
     rows, cols, tk = forge.forge_query_tile(512, 4096, 14336, I8)
     assert rows == 256            # an int8 tile is exactly one scale block tall
     assert forge.forge_query_tile(512, 4096, 4096, 3)[1] % 64 == 0   # row-block int8: whole 64-wide blocks
@@ -70,6 +71,22 @@ def test_query_tile():
     assert lib().forge_query_tile(512, 64, 64, 7, ctypes.byref(r), None, None) == DTYPE
     assert lib().forge_query_tile(-1, 64, 64, BF16, ctypes.byref(r), None, None) == SHAPE
     assert lib().forge_query_tile(512, 64, -8, BF16, None, None, None) == SHAPE
+
+
+@pytest.mark.skipif(torch.cuda.is_available() and torch.cuda.get_device_properties(0).multi_processor_count != 256,
+                    reason="the rows are those of 256 compute units")
+@pytest.mark.parametrize("md,T,d_in,d_out,tile", [
+    (I8, 512, 4096, 14336, (256, 128, 32)), (I8, 512, 3072, 4096, (256, 128, 32)),     # 384 tiles of 256 x 128
+    (I8, 512, 3072, 3840, (256, 64, 32)), (I8, 1023, 2048, 4096, (256, 64, 32)),
+    (I8, 1024, 2048, 4096, (256, 128, 32)), (I8, 4096, 2048, 2048, (256, 64, 32)), (I8, 0, 0, 8, (256, 64, 32)),
+    (BF16, 4096, 4096, 14336, (128, 256, 32)), (BF16, 512, 4096, 14336, (128, 128, 32)),
+    (BF16, 4096, 4096, 4096, (128, 128, 32)), (0, 4096, 4096, 14336, (128, 256, 32)),
+    (3, 512, 4096, 14336, (128, 256, 32)), (3, 256, 4096, 14336, (128, 128, 32)),
+    (4, 4096, 4096, 14336, (128, 256, 32)), (4, 4096, 1024, 1024, (128, 128, 32)),
+    (BF16, 2**63 - 1, 2**63 - 1, 2**63 - 1, (128, 256, 32)),                            # no size overflows the rule
+], ids=str)
+def test_query_tile_answers_what_the_step_runs(md, T, d_in, d_out, tile):
+    assert forge.forge_query_tile(T, d_in, d_out, md) == tile
 
 
 def test_dtype_errors():
