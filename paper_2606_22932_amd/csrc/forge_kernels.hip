@@ -1589,10 +1589,12 @@ struct WideLoop {
         mma(f1);
     }
 
-    // Rows ip*32 .. +31 of this wave's part to LDS as G[p][q] (fp32, pitch GP floats).
+    // Rows ip*32 .. +31 of this wave's part to LDS as G[p][q] (fp32, pitch GP floats).  Other
+    // lanes of the wave read what this one writes, before and after: wave_lds_order().
     template <int GP>
     __device__ __forceinline__ void stage_g(float *Gs, int ip, int lane) const
     {
+        wave_lds_order();
 #pragma unroll
         for (int iq = 0; iq < NA; ++iq)
 #pragma unroll
@@ -1601,6 +1603,7 @@ struct WideLoop {
                 const f32x4_t v = {x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]};
                 *reinterpret_cast<f32x4_t *>(Gs + (lane & 31) * GP + iq * 32 + g * 8 + (lane >> 5) * 4) = v;
             }
+        wave_lds_order();
     }
 };
 
