@@ -951,13 +951,14 @@ struct EpiQ {
     }
 
     Hyper hk;                      // the recurrence's constants with the decode scales folded in
+    float v_dec;                   // decode scale of sqrt(v)
     float w_inv, m_inv, v_inv;     // encode factors
     float aw, am, av;              // maxima so far
 
     __device__ __forceinline__ void begin(const Args &a)
     {
         const int enc = (a.slot + 3) % AMAX_SLOTS, dec = (a.slot + 2) % AMAX_SLOTS;
-        float w_dec = 1.0f, m_dec = 1.0f, v_dec = 1.0f;
+        float w_dec = 1.0f, m_dec = 1.0f;
         if constexpr (WF8) {
             w_dec = Fp8::scale_of(a.wr[dec]);
             w_inv = 1.0f / Fp8::scale_of(a.wr[enc]);
@@ -968,12 +969,12 @@ struct EpiQ {
             v_dec = Fp8::scale_of(a.vs[dec]);
             v_inv = 1.0f / Fp8::scale_of(a.vs[enc]);
         }
-        // A decode scale multiplies its code by way of the recurrence's constant: m' = (b1 s)
-        // q + c1 g, v' = (b2 s^2) q^2 + c2 g^2 (q^2 is exact), W' = (wdf s) q - update.
+        // The decode scales of m and W multiply their codes by way of the recurrence's constants:
+        // m' = (b1 s) q + c1 g, W' = (wdf s) q - update.  That of sqrt(v) does not: b2 s^2 would
+        // be subnormal from scales of 1e-19 down, where v itself is not.
         hk = a.h;
         hk.wdf = WF8 ? a.h.wdf * w_dec : a.h.wdf;
         hk.b1 = MF8 ? a.h.b1 * m_dec : a.h.b1;
-        hk.b2 = MF8 ? a.h.b2 * v_dec * v_dec : a.h.b2;
         aw = am = av = 0.0f;
     }
 
@@ -998,7 +999,8 @@ struct EpiQ {
             const float g = e < 4 ? g0[e] : g1[e - 4];
             if constexpr (!WF8) w0[e] = bf(pw16[i], e);
             if constexpr (MF8) {
-                v0[e] *= v0[e];
+                const float r0 = v_dec * v0[e];
+                v0[e] = r0 * r0;
             } else {
                 m0[e] = bf(pm16[i], e);
                 v0[e] = bf(pv16[i], e);
@@ -1174,12 +1176,11 @@ struct EpiAdamWI8 {
     __device__ __forceinline__ void state_at(const Args &a, int i, const float *g, int e,
                                              float &w1, float &m1, float &v1, float &rv1) const
     {
-        const float qv = code_at(pv[i], e);
+        const float r0 = sv[e] * code_at(pv[i], e);
         const float w0 = (e & 1) ? bf_hi(pw[i][e >> 1]) : bf_lo(pw[i][e >> 1]);
         Hyper hk = a.h;
         hk.b1 = sm[e];
-        hk.b2 = sv[e];
-        adamw_elem(g[e], w0, code_at(pm[i], e), qv * qv, hk, w1, m1, v1, rv1);   // qv * qv is exact
+        adamw_elem(g[e], w0, code_at(pm[i], e), r0 * r0, hk, w1, m1, v1, rv1);
     }
 
     // Contains one LDS barrier (the cross-wave absmax), which every wave of the
@@ -1192,12 +1193,10 @@ struct EpiAdamWI8 {
         float am[8], av[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) am[e] = av[e] = 0.0f;
-        // the scales multiply the codes by way of the recurrence's constants: b1 s_m, b2 s_v^2
+        // m's scales multiply the codes by way of the recurrence's constant, b1 s (not so those
+        // of sqrt(v): b2 s^2 would be subnormal from scales of 1e-19 down, where v is not)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            sm[e] *= a.h.b1;
-            sv[e] *= a.h.b2 * sv[e];
-        }
+        for (int e = 0; e < 8; ++e) sm[e] *= a.h.b1;
 
         // pass 1: weight update (from the unquantised fp32 state) and block absmax
 #pragma unroll
@@ -1800,14 +1799,11 @@ struct StreamI8 {
         else load_scales(a, p0, q0, s);
     }
 
-    // The scales multiply the codes by way of the recurrence's constants: b1 s_m, b2 s_v^2.
+    // m's scales multiply the codes by way of the recurrence's constant (EpiAdamWI8::run).
     __device__ __forceinline__ void fold_scales(const Hyper &h)
     {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            sm[e] *= h.b1;
-            sv[e] *= h.b2 * sv[e];
-        }
+        for (int e = 0; e < 8; ++e) sm[e] *= h.b1;
     }
 
     // Wait once for the slot's loads (issued a period earlier, so long done), then hide
@@ -1855,12 +1851,12 @@ struct StreamI8 {
     __device__ __forceinline__ void state_at(const Hyper &h, int i, float g, int e, float &w1, float &m1,
                                              float &v1, float &rv1) const
     {
-        const float qm = EpiAdamWI8<BP_I8, BQ_I8>::code_at(cm[i], e), qv = EpiAdamWI8<BP_I8, BQ_I8>::code_at(cv[i], e);
+        const float qm = EpiAdamWI8<BP_I8, BQ_I8>::code_at(cm[i], e);
+        const float r0 = sv[e] * EpiAdamWI8<BP_I8, BQ_I8>::code_at(cv[i], e);
         const float w0 = (e & 1) ? bf_hi(w[i][e >> 1]) : bf_lo(w[i][e >> 1]);
         Hyper hk = h;
         hk.b1 = sm[e];
-        hk.b2 = sv[e];
-        adamw_elem(g, w0, qm, qv * qv, hk, w1, m1, v1, rv1);   // qv * qv is exact
+        adamw_elem(g, w0, qm, r0 * r0, hk, w1, m1, v1, rv1);
     }
 
     // Pass 1, row I of tile (p0, q0), from the unquantised fp32 state: W' is stored, m'
@@ -2129,7 +2125,7 @@ struct WideI8 {
     static constexpr int RED = 4 * BQ_WI8;               // absmax partials of m, then of sqrt(v): [wave][column]
     u32x4_t pw[AH];
     u32x2_t pm[AH], pv[AH];
-    float km[8], kv[8];                                  // b1 s_m and b2 s_v^2 of this lane's columns
+    float km[8], kv[8];                                  // b1 s_m and s_v of this lane's columns
     float am[8], av[8];                                  // absmax so far; then the new scales' reciprocals
 
     // State of row pass i of the wave's sixteen (rows p + 4 i ..) into slot i % AH.
@@ -2167,7 +2163,6 @@ struct WideI8 {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             km[e] *= h.b1;
-            kv[e] *= h.b2 * kv[e];
             am[e] = av[e] = 0.0f;
         }
     }
@@ -2185,12 +2180,11 @@ struct WideI8 {
             using C = EpiAdamWI8<BP_I8, BQ_I8>;
             const float g = e < 4 ? g0[e] : g1[e - 4];
             const float w = (e & 1) ? bf_hi(pw[k][e >> 1]) : bf_lo(pw[k][e >> 1]);
-            const float qv = C::code_at(pv[k], e);
+            const float r0 = kv[e] * C::code_at(pv[k], e);
             Hyper hk = h;
             hk.b1 = km[e];
-            hk.b2 = kv[e];
             float v1;
-            adamw_elem(g, w, C::code_at(pm[k], e), qv * qv, hk, wo[e], mo[e], v1, ro[e]);   // qv * qv is exact
+            adamw_elem(g, w, C::code_at(pm[k], e), r0 * r0, hk, wo[e], mo[e], v1, ro[e]);
         }
     }
 
