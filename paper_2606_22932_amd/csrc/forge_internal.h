@@ -48,6 +48,7 @@ struct GroupArgs {
     Args a[MAX_GROUP];
     int start[MAX_GROUP + 1];
     int n;
+    int steady;            // token loop without tests (Mainloop::body)
 };
 
 // One term dY_s W_s of the input gradient (forge_dx.hip): dY_s bf16 [T, d_out],

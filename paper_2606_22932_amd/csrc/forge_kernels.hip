@@ -265,31 +265,49 @@ struct Mainloop {
             if (c < nch) issue(a, lds + c * STAGE_BYTES, c, wave);
     }
 
-    __device__ __forceinline__ void refill(const Args &a, unsigned char *lds, int c, int nch, int wave)
+    // The products of chunk c, in its stage.
+    __device__ __forceinline__ void chunk(uint32_t lds_base, int c)
     {
-        if (c + NS - 1 < nch) issue(a, lds + ((c + NS - 1) % NS) * STAGE_BYTES, c + NS - 1, wave);
+#pragma unroll
+        for (int h = 0; h < TK / 32; ++h)    // 32 tokens per compute(); X and Y rows of equal length
+            compute(lds_base + (uint32_t)((c % NS) * STAGE_BYTES + h * 32 * XROWB));
     }
 
     // The token loop of a tile started with begin(); executes exactly nch(T) workgroup
-    // barriers (one per chunk).  Behind a chunk's barrier every wave is done with the chunk
-    // before it, whose stage EARLY refills at once, before the products: the loop waits on this
-    // DMA (bf16 state at T = 512, with the refill behind the products: gate and up, 28672 x
-    // 4096, 279.6 against 275.5 us, 128256 x 4096 1206 against 1187 us; int8 columns, 552 x 6216
-    // at T = 2048, 67.0 against 65.8 us).  Short launches of bf16 state measured the other way
-    // (launch_group).
-    template <bool EARLY>
-    __device__ __forceinline__ void body(const Args &a, unsigned char *lds, int wave)
+    // barriers (one per chunk).  A workgroup waits on its own chain of chunks, and tests for the
+    // last ones in the loop cut a chunk's code in pieces and hold the refill back behind all of
+    // its products; the chunks that refill a stage therefore have a loop of their own.
+    // Microseconds, tests in every chunk against this: 1024 wide, 512 high, T = 2048 bf16 state
+    // 24.9 : 21.5, int8 columns 34.2 : 30.5; 2048 x 2048 28.7 : 27.2 and 36.7 : 32.5.  Where the
+    // launch asks for it (MAY_TEST and !steady: two workgroups of long loops on a CU, which share
+    // its operand DMA; launch_group) and with less than two rings of chunks, whose time is the
+    // fetch of the code, the loop keeps the tests.
+    template <bool MAY_TEST>
+    __device__ __forceinline__ void body(const Args &a, unsigned char *lds, int wave, bool steady)
     {
         const int nch = (a.T + TK - 1) / TK;
-        const uint32_t lds_base = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)lds;
-        for (int c = 0; c < nch; ++c) {
-            const int younger = min(NS - 2, nch - 1 - c);
-            wait_chunk(younger);
-            if constexpr (EARLY) refill(a, lds, c, nch, wave);
-#pragma unroll
-            for (int h = 0; h < TK / 32; ++h)    // 32 tokens per compute(); X and Y rows of equal length
-                compute(lds_base + (uint32_t)((c % NS) * STAGE_BYTES + h * 32 * XROWB));
-            if constexpr (!EARLY) refill(a, lds, c, nch, wave);
+        uint32_t lds_base = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)lds;
+        asm volatile("" : "+s"(lds_base));   // not again for every chunk, with the test for null
+        auto refill = [&](int c) { issue(a, lds + ((c + NS - 1) % NS) * STAGE_BYTES, c + NS - 1, wave); };
+        if (MAY_TEST && (!steady || nch < 2 * NS)) {
+            for (int c = 0; c < nch; ++c) {
+                const bool more = c + NS - 1 < nch;
+                if (__builtin_expect(more, 1)) wait_chunk(NS - 2);
+                else wait_chunk(nch - 1 - c);
+                chunk(lds_base, c);
+                if (__builtin_expect(more, 1)) refill(c);
+            }
+            return;
+        }
+        int c = 0;
+        for (; c + NS - 1 < nch; ++c) {
+            wait_chunk(NS - 2);
+            chunk(lds_base, c);
+            refill(c);
+        }
+        for (; c < nch; ++c) {
+            wait_chunk(nch - 1 - c);
+            chunk(lds_base, c);
         }
     }
 
@@ -299,13 +317,12 @@ struct Mainloop {
     // of them in the CU's vector memory path.  Without state to load (the store-G
     // epilogue) it only delays the mainloop: 1.5 % on the 4096 x 4096 store-G GEMM at
     // T = 4096.
-    template <bool EARLY>
     __device__ __forceinline__ void run(const Args &a, int p0, int q0, unsigned char *lds, int wave,
-                                        int lane, bool lead)
+                                        int lane, bool lead, bool steady)
     {
         begin(a, p0, q0, lds, wave, lane);
         if (lead) lds_barrier();
-        body<EARLY>(a, lds, wave);
+        body<true>(a, lds, wave, steady);
         lds_barrier();   // every wave is done reading the stages, which G reuses
     }
 
@@ -1338,7 +1355,7 @@ __device__ __forceinline__ void epi_store_g(const Args &a, int p0, int q0, int s
 
 // At most 128 VGPRs (four waves per SIMD): two 512-thread workgroups per CU, one math and
 // one stream wave of each on every SIMD.  At 129-136 registers only one would fit.
-template <int BP, int BQ, int MK, int EPI, int AH = 0, bool EARLY = true>
+template <int BP, int BQ, int MK, int EPI, int AH = 0>
 __global__ void __launch_bounds__(NT, 4) fused_kernel(GroupArgs g)
 {
     static_assert(MK != MK_I8, "int8 moments run in pipelined_i8_kernel");
@@ -1371,7 +1388,7 @@ __global__ void __launch_bounds__(NT, 4) fused_kernel(GroupArgs g)
     const int p0 = tp * BP, q0 = tq * BQ;
     if (wave < 4) {
         ML ml;
-        ml.template run<EARLY>(a, p0, q0, smem, wave, lane, LEAD);
+        ml.run(a, p0, q0, smem, wave, lane, LEAD, g.steady);
         ml.template stage_g<EM::GP>(Gs, wave, lane);
         lds_barrier();
         if constexpr (Q8) lds_barrier();
@@ -1414,7 +1431,9 @@ __global__ void __launch_bounds__(NT, 4) fused_kernel(GroupArgs g)
 // Token loop: a ring of three 24 KB stages (32 tokens).  The fragments of a 16-token step are
 // read from LDS while the matrix instructions of the step before run, across chunks too; one
 // barrier per chunk, in the middle of its products: behind it the next chunk has landed for
-// every wave, and the stage that it frees is refilled.
+// every wave, and the stage that it frees is refilled.  The last chunks, which refill nothing,
+// have a loop of their own: tests for them in every chunk cost 1-8 % (bf16 state, T = 2048, 4096
+// wide and 6144 high 136.2 : 130.0 us, 14336 high 301.6 : 289.2 us).
 template <int BP_, int BQ_>
 struct WideLoop {
     static constexpr int BP = BP_, BQ = BQ_, TK = 32, NS = 3;
@@ -1565,22 +1584,28 @@ struct WideLoop {
         asm volatile("s_barrier" ::: "memory");
         read<0>(f0, base);
         settle(f0);
-        for (int c = 0; c + 1 < nch; ++c) {
-            read<1>(f1, base + (uint32_t)((c % NS) * STAGE));
+        uint32_t st = base;                                  // stage of chunk c
+        // Chunk c, and the first reads of the next; refill() may fetch into the stage it frees.
+        auto step = [&](int younger, auto refill) {
+            read<1>(f1, st);
             mma(f0);
             __builtin_amdgcn_sched_barrier(0);
-            wait_dma(min(NS - 2, nch - 2 - c));
+            wait_dma(younger);
             settle(f1);
             // every wave has read stage c, and chunk c + 1 has landed
             asm volatile("s_barrier" ::: "memory");
-            read<0>(f0, base + (uint32_t)(((c + 1) % NS) * STAGE));
-            if (c + NS < nch) issue(a, lds, c + NS, wave);
+            st = st == base + (NS - 1) * STAGE ? base : st + STAGE;
+            read<0>(f0, st);
+            refill();
             __builtin_amdgcn_sched_barrier(0);
             mma(f1);
             __builtin_amdgcn_sched_barrier(0);
             settle(f0);
-        }
-        read<1>(f1, base + (uint32_t)(((nch - 1) % NS) * STAGE));
+        };
+        int c = 0;
+        for (; c + NS < nch; ++c) step(NS - 2, [&]() { issue(a, lds, c + NS, wave); });
+        for (; c + 1 < nch; ++c) step(nch - 2 - c, []() {});
+        read<1>(f1, st);
         mma(f0);
         __builtin_amdgcn_sched_barrier(0);
         settle(f1);
@@ -2070,7 +2095,7 @@ __global__ void __launch_bounds__(NT_I8P, NT_I8P / 256) pipelined_i8_kernel(Grou
         locate(0, mi, p0, q0);
         ml.begin(g.a[mi], p0, q0, ring, wave, lane);
         for (int k = 0; k < K; ++k) {
-            ml.template body<true>(g.a[mi], ring, wave);
+            ml.template body<false>(g.a[mi], ring, wave, true);
             for (int c = nch; c < nb; ++c) lds_barrier();
             lds_barrier();                                   // H1: the stream waves hold G(k-1)
             ml.template stage_g<EM::GP>(Gs, wave, lane);
@@ -2375,6 +2400,7 @@ static GroupArgs group_of(const Args *a, int n, int bp, int bq, int group_p)
 {
     GroupArgs g;
     g.n = n;
+    g.steady = 1;
     g.start[0] = 0;
     for (int i = 0; i < n; ++i) {
         int nt;
@@ -2439,8 +2465,13 @@ static hipError_t launch_group(const Args *a, int n, hipStream_t st)
     // fp32 state and short token loops: below.
     int rows = MK == MK_I8R64 ? 8 : 0;
     if (MK == MK_F32 && a[0].T < 1024) rows = raster_rows_f32(a, n, BP, BQ);
-    const GroupArgs g = group_of(a, n, BP, BQ, rows);
+    GroupArgs g = group_of(a, n, BP, BQ, rows);
     if (g.start[n] == 0) return hipSuccess;
+    // Two workgroups on a CU with long loops share its operand DMA, and chunks that are refilled
+    // later, behind the tests, get through it faster.  bf16 AdamW, microseconds: 4096 wide, 2048
+    // high, T = 4096 73.0 against 75.6, 4096 x 4096, T = 2048 89.8 : 93.6; at T = 1024 60.3 : 59.1,
+    // and with one workgroup per CU (2048 x 2048, T = 2048) 28.7 : 27.2.
+    if (a[0].T >= 2048 && g.start[n] > device_cu_count()) g.steady = 0;
     // Prefetch depth by launch length (AdamW on bf16 state): a launch of at least 8 waves of
     // resident tiles, or with a long token loop (T >= 1024), loads all eight
     // row passes of a tile's state during its mainloop, a shorter one six.  Measured per
@@ -2451,15 +2482,6 @@ static hipError_t launch_group(const Args *a, int n, hipStream_t st)
     if constexpr (MK == MK_BF16 && EPI == EPI_ADAMW)
         if (g.start[n] >= 8 * 2 * device_cu_count() || a[0].T >= 1024) {
             hipLaunchKernelGGL((fused_kernel<BP, BQ, MK, EPI, 8>), dim3(g.start[n]), dim3(NT), 0, st, g);
-            return hipGetLastError();
-        }
-    // Launches of less than four waves of resident tiles refill the operand ring behind a chunk's
-    // products (Mainloop::body).  Behind against before, bf16 AdamW at T = 512, microseconds:
-    // 4096 x 4096 (2 waves) 48.9 : 49.2, dX and the step of q, k and v (3) 112.5 : 112.9; of
-    // 4096 x 14336 (7) 243.6 : 241.4.
-    if constexpr (MK == MK_BF16 && EPI == EPI_ADAMW)
-        if (g.start[n] < 4 * 2 * device_cu_count()) {
-            hipLaunchKernelGGL((fused_kernel<BP, BQ, MK, EPI, 0, false>), dim3(g.start[n]), dim3(NT), 0, st, g);
             return hipGetLastError();
         }
     hipLaunchKernelGGL((fused_kernel<BP, BQ, MK, EPI>), dim3(g.start[n]), dim3(NT), 0, st, g);

@@ -138,17 +138,20 @@ def test_long_loop_group_equals_single_steps_bitwise():
         assert all(torch.equal(s, t) for s, t in zip(x[2:], y[2:]))
 
 
-@pytest.mark.parametrize("T", [33, 97, 224])
-def test_refill_order_is_bitwise_neutral(T):
-    """Four waves of resident tiles (on 256 CUs 2048 of 128 x 128; here 65 x 33) and up refill the
-    operand ring before a chunk's products, shorter launches (the slices) behind them: fewer chunks
-    than the ring has stages, one more, and a ring that goes around."""
+@pytest.mark.parametrize("T", [33, 97, 224, 2049])
+def test_token_loop_forms_are_bitwise_neutral(T):
+    """The 128 x 128 kernel's token loop has two forms: with tests in every chunk (less than two
+    rings of chunks; T >= 2048 on more than 256 tiles, which here is the whole of 17 x 25) and
+    without (the slices of at most 8 x 25 from T = 225 on).  Fewer chunks than the ring has stages,
+    one more, a ring that goes around, and one form against the other."""
     print("case", T, flush=True)
+    d_in, d_out = (D_IN, D_OUT) if T < 2048 else (3208, 2168)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(14)
-    X, dY = _gauss((T, D_IN), 1.0, gen), _gauss((T, D_OUT), 1e-3, gen)
-    whole = _state("bf16", D_OUT, gen)
-    parts = {r0: {k: t[r0:r0 + SLICE].clone() for k, t in whole.items()} for r0 in range(0, D_OUT, SLICE)}
+    X, dY = _gauss((T, d_in), 1.0, gen), _gauss((T, d_out), 1e-3, gen)
+    whole = {"W": _gauss((d_out, d_in), 0.02, gen), "m": _gauss((d_out, d_in), 1e-4, gen),
+             "v": _gauss((d_out, d_in), 1e-6, gen).abs_()}
+    parts = {r0: {k: t[r0:r0 + SLICE].clone() for k, t in whole.items()} for r0 in range(0, d_out, SLICE)}
     _step("bf16", X, dY, whole)
     for r0, s in parts.items():
         _step("bf16", X, dY[:, r0:r0 + SLICE].contiguous(), s)
