@@ -373,25 +373,31 @@ __global__ void __launch_bounds__(64 * NW, (BK == 64 || NW > 4) ? 1 : 2) dx_kern
     tile.store(g, t0, q0, smem, wave, lane, tid);
 }
 
-// Token rows per tile, by the rounds of tiles that the chip needs.  Cost of a tile per row of K,
-// in 10 ps (measured on d_in 776-14336 at T = 64-4096): 64 x 128 tiles, one per CU, 62 a round;
-// 128 x 128 tiles 114 with one per CU, 177 with two; 256 x 256 tiles, one per CU, 237 in a round
-// that leaves CUs idle, 293 in a full one (the clock drops).  Against the largest tile whose
-// grid covers the CUs, microseconds: d_in = 14336, d_out = 4096 at T = 1024 118 : 166, at
-// T = 256 57 : 65; 8192 x 8192 at T = 1536 201 : 264, at T = 333 90 : 103; 4160 x 4160 at T = 512
-// 47 : 52, at T = 4096 182 : 213; 4096 x 4096 at T = 777 48 : 54.  Every choice sums over K in the
-// same order: dX is the same bits whichever tile computes it.
-static int dx_rows(int T, int d_in)
+// Token rows per tile, by the rounds of tiles that the chip needs.  A round costs 2.4 us, what its
+// tiles take to start and to store, and per row of K, in units of 0.1 ns (measured on d_in 256-14336,
+// K 256-14280, T = 64-4096): 64 x 128 tiles, one per CU, 62; 128 x 128 tiles 114 with one per CU,
+// 177 with two; 256 x 256 tiles, one per CU, 237 in a round that leaves CUs idle, 293 in a full one
+// (the clock drops).  Against the largest tile whose grid covers the CUs, microseconds: d_in = 14336,
+// K = 4096 at T = 1024 118 : 166, at T = 256 57 : 65; 8192 x 8192 at T = 1536 201 : 264, at T = 333
+// 90 : 103; 4160 x 4160 at T = 512 47 : 52, at T = 4096 182 : 213; 4096 x 4096 at T = 777 48 : 54; over
+// 474 drawn sizes 2.7 % faster on average, and slower on a few: d_in = 1384, K = 7848, T = 1715
+// 116 : 99, d_in = 6328, K = 944, T = 2688 62 : 59.  Without the constant, short sums and large grids
+// took too many rounds of small tiles: d_in = 4688, K = 288, T = 805 10.4 : 9.0, d_in = 12944,
+// K = 2280, T = 2624 217 : 191, d_in = 11512, K = 4096, T = 3032 373 : 338.
+// Every choice sums over K in the same order: dX is the same bits whichever tile computes it.
+static int dx_rows(int T, int d_in, int64_t K)
 {
     if (FORGE_DX_BT) return FORGE_DX_BT;
-    const long cus = device_cu_count();
-    auto tiles = [&](long bt, long bq) { return (T + bt - 1) / bt * ((d_in + bq - 1) / bq); };
-    const long n64 = tiles(64, DX_BQ), n128 = tiles(128, DX_BQ), n256 = tiles(256, 256);
-    const long c64 = (n64 + cus - 1) / cus * 62;
+    const int64_t cus = device_cu_count();
+    auto tiles = [&](int64_t bt, int64_t bq) { return (T + bt - 1) / bt * ((d_in + bq - 1) / bq); };
+    auto round = [&](int64_t per_row) { return per_row * K + 24000; };
+    const int64_t n64 = tiles(64, DX_BQ), n128 = tiles(128, DX_BQ), n256 = tiles(256, 256);
+    const int64_t c64 = (n64 + cus - 1) / cus * round(62);
     // a remainder behind full rounds costs less than a round only if it is small
-    const long f128 = n128 / (2 * cus), r128 = n128 % (2 * cus);
-    const long c128 = f128 * 177 + (r128 == 0 ? 0 : r128 <= (f128 ? cus / 2 : cus) ? 114 : 177);
-    const long c256 = n256 / cus * 293 + (n256 % cus == 0 ? 0 : 237);
+    const int64_t f128 = n128 / (2 * cus), r128 = n128 % (2 * cus);
+    const int64_t c128 = f128 * round(177) +
+                         (r128 == 0 ? 0 : round(r128 <= (f128 ? cus / 2 : cus) ? 114 : 177));
+    const int64_t c256 = n256 / cus * round(293) + (n256 % cus == 0 ? 0 : round(237));
     if (c256 <= c128 && c256 <= c64) return 256;
     return c128 <= c64 ? 128 : 64;
 }
@@ -403,7 +409,9 @@ hipError_t launch_dx(const DxSeg *s, int n, uint16_t *dX, int T, int d_in, hipSt
     g.n = n;
     g.nch = 0;
     for (int i = 0; i < MAX_GROUP; ++i) g.s[i] = i < n ? s[i] : DxSeg{nullptr, nullptr, 0};
-    const int bt = dx_rows(T, d_in);
+    int64_t K = 0;
+    for (int i = 0; i < n; ++i) K += s[i].d_out;
+    const int bt = dx_rows(T, d_in, K);
     const int bk = bt == 64 ? 64 : 32;
     for (int i = 0; i < n; ++i) g.nch += (s[i].d_out + bk - 1) / bk;
     g.dX = dX;
