@@ -2430,21 +2430,28 @@ static bool wide_pays(int mk, int epi, int64_t T, int64_t tiles)
     return T >= (w8 || mk == MK_I8R64 || mk == MK_FP8 ? 512 : 1024);
 }
 
-// Raster rows for fp32 state, whose rows of 4 B elements span twice the memory of bf16's: 4, so
-// that an XCD's tiles lie in few, whole rows of the state, or all of them on grids of at most
-// 32 x 32 tiles (and more than 16 high).  Matrices less than 2048 wide keep the shape rule
-// (1024 x 4096 with all rows 18.9 : 17.2).  Against the shape rule at T = 512, microseconds, AdamW and SGD with momentum:
-// 8192 x 8192 291 : 317 and 198 : 201, 8192 x 2048 80 : 87 and 55 : 61, 14336 x 4096 244 : 245,
-// 1024 x 4096 24.1 : 25.4; 4096 x 4096 (all rows) 76 : 80 and 54 : 57 (with 4: 83 and 56).  Long
-// token loops keep the shape rule: their operand slabs want compact tile groups.
-static int raster_rows_f32(const Args *a, int n, int bp, int bq)
+// Raster rows of a matrix with fp32 state and a short token loop (0: the shape rule).  Rows of
+// 4-byte state span twice the memory of bf16's; groups of 4 keep an XCD's tiles in few, whole
+// rows.  Measured at T = 128 and 512 with AdamW, SGD with momentum and Lion on tile grids of 8 to
+// 112 by 8 to 112 (speed against the shape rule):
+// - Groups of 4 on widths that are no multiple of 4096: 0.97-1.03, 2048 wide 0.98-1.10 (8192 high
+//   1.1-1.5), 3072 wide and 11008 high 1.13-1.23, 6144 x 4096 1.04-1.07; but 11008 wide and 2048 or
+//   1024 high 0.93-0.97: not for matrices wider than tall of up to 16 tile rows.
+// - Widths that are multiples of 4096, whose rows all begin on the same memory channels: 1.00-1.07
+//   on taller matrices (8192 x 8192 1.01-1.16), but less where the matrix is wider than tall (4096
+//   wide, 2048 high 0.77-0.90; 8192 x 4096 0.92-0.97) or the runs of every other XCD begin in the
+//   middle of a group (4096 wide, 6144 high 0.88-0.92).
+// - 4096 wide and 25 to 33 tile rows high: all rows in one group, so that the XCDs begin on
+//   different columns: 0.99-1.07 from 25 to 31 and at 33, 1.07-1.36 at 32; at 34 and more groups
+//   of 4 are better, 3968 and 4224 wide it is 0.97-1.00.
+// Widths below 2048 keep the shape rule, and so do long token loops: their operand slabs want
+// compact tile groups.
+static int raster_rows_f32(int d_in, int tiles_p, int tiles_q)
 {
-    int rows = 32;
-    for (int i = 0; i < n; ++i) {
-        if (a[i].d_in < 16 * bq) return 0;
-        if (a[i].d_out > 32 * bp || a[i].d_in > 32 * bq || a[i].d_out <= 16 * bp) rows = 4;
-    }
-    return rows;
+    if (tiles_q < 16) return 0;
+    if (d_in % 4096 != 0) return tiles_p <= 16 && tiles_p < tiles_q ? 0 : 4;
+    if (d_in == 4096 && tiles_p > 24 && tiles_p <= 33) return tiles_p;
+    return tiles_p < tiles_q || tiles_p % 32 == 16 ? 0 : 4;
 }
 
 // The launch of n matrices (all with the same T).
@@ -2462,11 +2469,11 @@ static hipError_t launch_group(const Args *a, int n, hipStream_t st)
     }
     // int8 row-block state: groups of 8 tile rows (measured on the MLP projections at
     // T = 512: 5 % faster than the shape rule, whose 24-row groups suit bf16 state)
-    // fp32 state and short token loops: below.
-    int rows = MK == MK_I8R64 ? 8 : 0;
-    if (MK == MK_F32 && a[0].T < 1024) rows = raster_rows_f32(a, n, BP, BQ);
-    GroupArgs g = group_of(a, n, BP, BQ, rows);
+    GroupArgs g = group_of(a, n, BP, BQ, MK == MK_I8R64 ? 8 : 0);
     if (g.start[n] == 0) return hipSuccess;
+    if (MK == MK_F32 && a[0].T < 1024)
+        for (int i = 0; i < n; ++i)
+            if (const int rows = raster_rows_f32(a[i].d_in, g.a[i].tiles_p, g.a[i].tiles_q)) g.a[i].group_p = rows;
     // Two workgroups on a CU with long loops share its operand DMA, and chunks that are refilled
     // later, behind the tests, get through it faster.  bf16 AdamW, microseconds: 4096 wide, 2048
     // high, T = 4096 73.0 against 75.6, 4096 x 4096, T = 2048 89.8 : 93.6; at T = 1024 60.3 : 59.1,

@@ -159,3 +159,24 @@ def test_token_loop_forms_are_bitwise_neutral(T):
     for r0, s in parts.items():
         for k, t in s.items():
             assert torch.equal(whole[k][r0:r0 + SLICE], t), (k, r0)
+
+
+@pytest.mark.parametrize("d_in,d_out", [(2056, 4424), (4096, 3272), (4096, 6152), (4104, 1544)], ids=str)
+def test_fp32_rasters_are_bitwise_neutral(d_in, d_out):
+    """fp32 state with short loops walks its tiles in groups of 4 tile rows (here 35, a remainder of
+    3), in one group (26 rows of a 4096 wide matrix), and by the shape rule (49 and 13 rows): every
+    tile once, whatever the order."""
+    print("case", d_in, d_out, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(15)
+    X, dY = _gauss((33, d_in), 1.0, gen), _gauss((33, d_out), 1e-3, gen)
+    whole = {"W": _gauss((d_out, d_in), 0.02, gen), "m": _gauss((d_out, d_in), 1e-4, gen, torch.float32),
+             "v": _gauss((d_out, d_in), 1e-6, gen, torch.float32).abs_()}
+    parts = {r0: {k: t[r0:r0 + 896].clone() for k, t in whole.items()} for r0 in range(0, d_out, 896)}
+    _step("f32", X, dY, whole)
+    for r0, s in parts.items():
+        _step("f32", X, dY[:, r0:r0 + 896].contiguous(), s)
+    torch.cuda.synchronize()
+    for r0, s in parts.items():
+        for k, t in s.items():
+            assert torch.equal(whole[k][r0:r0 + 896], t), (k, r0)
