@@ -2415,19 +2415,27 @@ static GroupArgs group_of(const Args *a, int n, int bp, int bq, int group_p)
 }
 
 // Whether a launch of `tiles` 128 x 256 tiles with T tokens runs in wide_kernel, whose 2 * CUs
-// workgroups want at least two tiles each (measured over 2048-14336 wide shapes; ratio of the
-// 128 x 128 kernel's time to wide_kernel's).  T >= 1024: 1.02-1.10 (every rule and state; 14336
-// x 4096 with fp32 state 1.00), 1.25-1.30 at T = 4096; at T = 512 0.91-0.98 with bf16 and
-// fp32 state, but with 8-bit state, whose epilogue is short beside the loop, 1.00-1.12.  fp8
-// weights and moments gain from one tile per workgroup and T = 256 on (1.01-1.08).  With fewer
-// tiles the smaller tiles fill the chip better (2048 x 4096: 0.75-0.95).
-static bool wide_pays(int mk, int epi, int64_t T, int64_t tiles)
+// workgroups want at least two tiles each.  Ratio of the 128 x 128 kernel's time to wide_kernel's
+// over matrices 1024 to 14336 wide and high, cold operands:
+// - bf16 state, T = 1024: 1.07-1.11 where d_in >= d_out, 1.00-1.05 on 5000 wide, 7000 high and 4096
+//   wide, 8192 high, but 0.93-0.97 on 4096 wide, 12288 and 14336 high; there, T = 1280 0.89 (16384
+//   high) to 1.02 (28672 high), T = 1536 0.96-1.05, so not before: launches more than twice as
+//   high as wide.  T = 2048 1.0-1.15, T = 4096 1.1-1.4 (4096 wide, 8192 high 0.97-1.0).
+// - fp32 state, T = 1024: 0.87-0.99 (4096 wide, 8192 high 1.08), T = 1408 0.95-1.0, T = 2048
+//   1.01-1.10, T = 4096 1.09-1.27.
+// - 8-bit state, whose epilogue is short beside the loop: T = 512 1.00-1.12, T = 256 0.93-1.08.
+//   fp8 weights and moments gain from one tile per workgroup and T = 256 on (1.01-1.08).
+// With fewer tiles the smaller ones fill the chip better: 5120 x 5120 (800) 0.88-0.97, 4096 x 4096
+// (512) 0.79-0.95.
+static bool wide_pays(int mk, int epi, int64_t T, int64_t tiles, bool tall)
 {
     const int slots = 2 * device_cu_count();
     const bool w8 = epi == EPI_ADAMW_WFP8;
     if (w8 && mk == MK_FP8) return T >= 256 && tiles >= slots;
     if (tiles < 2 * slots) return false;
-    return T >= (w8 || mk == MK_I8R64 || mk == MK_FP8 ? 512 : 1024);
+    if (w8 || mk == MK_I8R64 || mk == MK_FP8) return T >= 512;
+    if (mk == MK_F32) return T >= 1536;
+    return T >= (tall ? 1536 : 1024);
 }
 
 // Raster rows of a matrix with fp32 state and a short token loop (0: the shape rule).  Rows of
@@ -2460,7 +2468,9 @@ static hipError_t launch_group(const Args *a, int n, hipStream_t st)
 {
     if constexpr (EPI != EPI_STORE_BF16 && EPI != EPI_STORE_F32) {
         const int tiles = count_tiles(a, n, BP_W, BQ_W), slots = 2 * device_cu_count();
-        if (wide_pays(MK, EPI, a[0].T, tiles)) {
+        int64_t high = 0;
+        for (int i = 0; i < n; ++i) high += a[i].d_out;
+        if (wide_pays(MK, EPI, a[0].T, tiles, high > 2 * (int64_t)a[0].d_in)) {
             // raster groups of 8 tile rows: against 4, 1-8 % faster on 8192 x 8192, even elsewhere
             const GroupArgs w = group_of(a, n, BP_W, BQ_W, 8);
             hipLaunchKernelGGL((wide_kernel<MK, EPI>), dim3(tiles < slots ? tiles : slots), dim3(NROLE), 0, st, w);
@@ -2476,9 +2486,9 @@ static hipError_t launch_group(const Args *a, int n, hipStream_t st)
             if (const int rows = raster_rows_f32(a[i].d_in, g.a[i].tiles_p, g.a[i].tiles_q)) g.a[i].group_p = rows;
     // Two workgroups on a CU with long loops share its operand DMA, and chunks that are refilled
     // later, behind the tests, get through it faster.  bf16 AdamW, microseconds: 4096 wide, 2048
-    // high, T = 4096 73.0 against 75.6, 4096 x 4096, T = 2048 89.8 : 93.6; at T = 1024 60.3 : 59.1,
-    // and with one workgroup per CU (2048 x 2048, T = 2048) 28.7 : 27.2.
-    if (a[0].T >= 2048 && g.start[n] > device_cu_count()) g.steady = 0;
+    // high, T = 4096 73.0 against 75.6, 6144 high, T = 1536 107 : 113; 4096 x 4096, T = 2048
+    // 89.8 : 93.6, T = 1024 60.3 : 59.1; with one workgroup per CU (2048 x 2048, T = 2048) 28.7 : 27.2.
+    if (a[0].T >= 1536 && g.start[n] > device_cu_count()) g.steady = 0;
     // Prefetch depth by launch length (AdamW on bf16 state): a launch of at least 8 waves of
     // resident tiles, or with a long token loop (T >= 1024), loads all eight
     // row passes of a tile's state during its mainloop, a shorter one six.  Measured per
@@ -2545,7 +2555,7 @@ TileShape tile_shape(int mk, int64_t T, int64_t d_in, int64_t d_out)
             return TileShape{BP_WI8, BQ_WI8, WideLoop<BP_WI8, BQ_WI8>::TK};
         return TileShape{BP_I8, BQ_I8, 32};
     }
-    if (wide_pays(mk, EPI_ADAMW, T, count_tiles(d_in, d_out, BP_W, BQ_W)))
+    if (wide_pays(mk, EPI_ADAMW, T, count_tiles(d_in, d_out, BP_W, BQ_W), d_out > 2 * d_in))
         return TileShape{BP_W, BQ_W, WideLoop<BP_W, BQ_W>::TK};
     return TileShape{BP_F, BQ_F, TK128};
 }

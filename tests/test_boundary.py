@@ -80,7 +80,10 @@ def test_query_tile():
     (I8, 512, 3072, 3840, (256, 64, 32)), (I8, 1023, 2048, 4096, (256, 64, 32)),
     (I8, 1024, 2048, 4096, (256, 128, 32)), (I8, 4096, 2048, 2048, (256, 64, 32)), (I8, 0, 0, 8, (256, 64, 32)),
     (BF16, 4096, 4096, 14336, (128, 256, 32)), (BF16, 512, 4096, 14336, (128, 128, 32)),
-    (BF16, 4096, 4096, 4096, (128, 128, 32)), (0, 4096, 4096, 14336, (128, 256, 32)),
+    (BF16, 4096, 4096, 4096, (128, 128, 32)), (BF16, 1535, 4096, 14336, (128, 128, 32)),
+    (BF16, 1536, 4096, 14336, (128, 256, 32)), (BF16, 1023, 14336, 4096, (128, 128, 32)),
+    (BF16, 1024, 14336, 4096, (128, 256, 32)), (0, 1535, 14336, 4096, (128, 128, 32)),
+    (0, 1536, 14336, 4096, (128, 256, 32)),
     (3, 512, 4096, 14336, (128, 256, 32)), (3, 256, 4096, 14336, (128, 128, 32)),
     (4, 4096, 4096, 14336, (128, 256, 32)), (4, 4096, 1024, 1024, (128, 128, 32)),
     (BF16, 2**63 - 1, 2**63 - 1, 2**63 - 1, (128, 256, 32)),                            # no size overflows the rule

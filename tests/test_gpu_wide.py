@@ -66,7 +66,7 @@ def _raw(t):
     return t.view(torch.uint8) if t.dtype == torch.float8_e4m3fn else t
 
 
-@pytest.mark.parametrize("kind,T", [("bf16", 1025), ("f32", 1056), ("i8r64", 513), ("fp8", 544), ("wfp8_bf16", 545),
+@pytest.mark.parametrize("kind,T", [("bf16", 1537), ("f32", 1568), ("bf16", 1025), ("f32", 1056), ("i8r64", 513), ("fp8", 544), ("wfp8_bf16", 545),
                                     ("wfp8_fp8", 257), ("i8", 0), ("i8", 1), ("i8", 70), ("i8", 513)])
 def test_long_loop_kernel_equals_row_slices_bitwise(kind, T):
     print("case", kind, T, flush=True)
@@ -95,7 +95,7 @@ def test_long_loop_kernel_equals_row_slices_bitwise(kind, T):
                                         ("muon_accumulate", torch.bfloat16)])
 def test_long_loop_rules_equal_row_slices_bitwise(rule, dtype):
     print("case", rule, dtype, flush=True)
-    T = 1031
+    T = 1543
     gen = torch.Generator(device="cuda")
     gen.manual_seed(12)
     X, dY = _gauss((T, D_IN), 1.0, gen), _gauss((T, D_OUT), 1e-3, gen)
@@ -121,7 +121,7 @@ def test_long_loop_rules_equal_row_slices_bitwise(rule, dtype):
 
 def test_long_loop_group_equals_single_steps_bitwise():
     """A group that only together is large enough for the long-loop kernel."""
-    T, d_in, d_outs = 1040, 2056, (7184, 264, 8200)
+    T, d_in, d_outs = 1552, 2056, (7184, 264, 8200)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(13)
     X = _gauss((T, d_in), 1.0, gen)
