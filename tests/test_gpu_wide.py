@@ -4,7 +4,7 @@ the 128 x 128 kernel, bit for bit.
 Steps are tile-local and every kernel sums a tile's products in the same order, so a matrix
 large enough for the long-loop kernel must end with the same bits as its row slices stepped one
 by one, which are too small for it; the kernel that steps the slices is checked against the
-oracle elsewhere.  Sizes leave remainders on every axis, more tiles than resident workgroups
+oracle elsewhere.  (bf16 at T = 1025 and fp32 at 1056 are below the rule: the other kernel's.)  Sizes leave remainders on every axis, more tiles than resident workgroups
 (a workgroup walks several tiles), and a last chunk of one token.
 """
 import pytest
@@ -22,27 +22,30 @@ def _gauss(shape, std, gen, dtype=torch.bfloat16):
     return torch.randn(shape, generator=gen, device="cuda").mul_(std).to(dtype)
 
 
-def _state(kind, rows, gen):
-    """State tensors of [rows, D_IN] by argument name."""
-    shape = (rows, D_IN)
+def _state(kind, rows, gen, d_in=D_IN):
+    """State tensors of [rows, d_in] by argument name."""
+    shape = (rows, d_in)
     codes = lambda lo, hi: torch.randint(lo, hi, shape, generator=gen, device="cuda", dtype=torch.int8)
-    fp8 = lambda lo, hi: torch.randint(lo, hi, shape, generator=gen, device="cuda",
-                                       dtype=torch.uint8).view(torch.float8_e4m3fn)
+    def fp8(signed):         # every finite code, of either sign or none
+        c = torch.randint(0, 0x7F, shape, generator=gen, device="cuda", dtype=torch.uint8)
+        if signed:
+            c |= torch.randint(0, 2, shape, generator=gen, device="cuda", dtype=torch.uint8) << 7
+        return c.view(torch.float8_e4m3fn)
     ring = lambda a: torch.tensor([0.0, 0.0, a, a], device="cuda")
     s = {"W": _gauss(shape, 0.02, gen)}
     if kind in ("bf16", "f32", "wfp8_bf16"):
         dt = torch.float32 if kind == "f32" else torch.bfloat16
         s["m"], s["v"] = _gauss(shape, 1e-4, gen, dt), _gauss(shape, 1e-6, gen, torch.float32).abs_().to(dt)
     elif kind in ("i8", "i8r64"):
-        sshape = ((rows + 255) // 256, D_IN) if kind == "i8" else (rows, (D_IN + 63) // 64)
+        sshape = ((rows + 255) // 256, d_in) if kind == "i8" else (rows, (d_in + 63) // 64)
         s["m"], s["v"] = codes(-127, 128), codes(1, 128)
         u = lambda x: torch.rand(sshape, generator=gen, device="cuda").add_(0.5).mul_(x / 127)
         s["ms"], s["vs"] = u(3e-4), u(3e-3 if kind == "i8" else 3e-6)
     else:
-        s["m"], s["v"] = fp8(0, 0x7F), fp8(0, 0x7F)
+        s["m"], s["v"] = fp8(True), fp8(False)
         s["ms"], s["vs"] = ring(3e-4), ring(3e-3)
     if kind.startswith("wfp8"):
-        s["W"], s["wr"] = fp8(0, 0x7F), ring(0.06)
+        s["W"], s["wr"] = fp8(True), ring(0.06)
     return s
 
 
@@ -63,17 +66,39 @@ def _rows(kind, name, t, r0, r1):
 
 
 def _raw(t):
-    return t.view(torch.uint8) if t.dtype == torch.float8_e4m3fn else t
+    """t as integers of its size, which compare NaNs too."""
+    return t.view({1: torch.uint8, 2: torch.int16, 4: torch.int32}[t.element_size()])
 
 
-@pytest.mark.parametrize("kind,T", [("bf16", 1537), ("f32", 1568), ("bf16", 1025), ("f32", 1056), ("i8r64", 513), ("fp8", 544), ("wfp8_bf16", 545),
-                                    ("wfp8_fp8", 257), ("i8", 0), ("i8", 1), ("i8", 70), ("i8", 513)])
+@pytest.mark.parametrize("kind,T", [("bf16", 1537), ("f32", 1568), ("bf16", 1025), ("f32", 1056), ("i8r64", 513),
+                                    ("fp8", 544), ("wfp8_bf16", 545), ("wfp8_fp8", 257), ("i8", 0), ("i8", 1),
+                                    ("i8", 70), ("i8", 513)])
 def test_long_loop_kernel_equals_row_slices_bitwise(kind, T):
     print("case", kind, T, flush=True)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(11)
     X, dY = _gauss((T, D_IN), 1.0, gen), _gauss((T, D_OUT), 1e-3, gen)
+    _whole_equals_slices(kind, X, dY, _state(kind, D_OUT, gen))
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")], ids=str)
+@pytest.mark.parametrize("kind,T", [("fp8", 544), ("wfp8_fp8", 257), ("i8", 70), ("i8r64", 513)])
+def test_long_loop_kernel_passes_nan_and_inf_like_row_slices(kind, T, bad):
+    """A NaN or Inf token makes a column of G NaN or infinite, and what a tile holds outside the
+    matrix NaN (zero times Inf): maxima pass NaNs by, and take no part of what is outside."""
+    print("case", kind, T, bad, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(16)
+    X, dY = _gauss((T, D_IN), 1.0, gen), _gauss((T, D_OUT), 1e-3, gen)
+    X[T - 1, 17] = X[3, D_IN - 1] = bad
+    dY[5, D_OUT - 9] = float("nan")
     whole = _state(kind, D_OUT, gen)
+    _whole_equals_slices(kind, X, dY, whole)
+    if "fp8" in kind:
+        assert bool(torch.isfinite(whole["ms"][0])) == (bad != bad) and float(whole["vs"][0]) > 0
+
+
+def _whole_equals_slices(kind, X, dY, whole):
     parts = []
     for r0 in range(0, D_OUT, SLICE):
         r1 = min(r0 + SLICE, D_OUT)
@@ -92,7 +117,10 @@ def test_long_loop_kernel_equals_row_slices_bitwise(kind, T):
 
 
 @pytest.mark.parametrize("rule,dtype", [("sgd_momentum", torch.float32), ("nadam", torch.bfloat16),
-                                        ("muon_accumulate", torch.bfloat16)])
+                                        ("muon_accumulate", torch.bfloat16), ("sgd", torch.bfloat16),
+                                        ("adagrad", torch.float32), ("rmsprop", torch.bfloat16),
+                                        ("lion", torch.bfloat16), ("radam", torch.float32),
+                                        ("adamax", torch.bfloat16)])
 def test_long_loop_rules_equal_row_slices_bitwise(rule, dtype):
     print("case", rule, dtype, flush=True)
     T = 1543
@@ -119,23 +147,26 @@ def test_long_loop_rules_equal_row_slices_bitwise(rule, dtype):
             assert torch.equal(t[a:b], u), a
 
 
-def test_long_loop_group_equals_single_steps_bitwise():
-    """A group that only together is large enough for the long-loop kernel."""
-    T, d_in, d_outs = 1552, 2056, (7184, 264, 8200)
+@pytest.mark.parametrize("kind,T", [("bf16", 1552), ("i8", 70), ("i8r64", 520), ("fp8", 520)])
+def test_long_loop_group_equals_single_steps_bitwise(kind, T):
+    """A group that only together is large enough for the long-loop kernel (int8 columns: with a
+    matrix that alone is not); a workgroup goes from one matrix to the next, with its own scales
+    and amax ring."""
+    print("case", kind, T, flush=True)
+    d_in, d_outs = 2056, (7184, 264, 8200)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(13)
     X = _gauss((T, d_in), 1.0, gen)
-    mats = []
-    for d in d_outs:
-        m, v = _gauss((d, d_in), 1e-4, gen), _gauss((d, d_in), 1e-6, gen).abs_()
-        mats.append((X, _gauss((T, d), 1e-3, gen), _gauss((d, d_in), 0.02, gen), m, v))
-    alone = [(X, b[1]) + tuple(t.clone() for t in b[2:]) for b in mats]
-    forge.forge_linear_step_grouped(mats, step=100, **HP)
-    for b in alone:
-        forge.forge_linear_step(*b, step=100, **HP)
+    mats = [(_gauss((T, d), 1e-3, gen), _state(kind, d, gen, d_in)) for d in d_outs]
+    alone = [(dY, {k: t.clone() for k, t in s.items()}) for dY, s in mats]
+    forge.forge_linear_step_grouped([(X, dY, s["W"], s["m"], s["v"], s.get("ms"), s.get("vs")) for dY, s in mats],
+                                    step=100, **HP)
+    for dY, s in alone:
+        _step(kind, X, dY, s)
     torch.cuda.synchronize()
-    for x, y in zip(mats, alone):
-        assert all(torch.equal(s, t) for s, t in zip(x[2:], y[2:]))
+    for (_, x), (_, y) in zip(mats, alone):
+        for k in x:
+            assert torch.equal(_raw(x[k]), _raw(y[k])), k
 
 
 @pytest.mark.parametrize("T", [33, 97, 224, 2049])

@@ -1,10 +1,11 @@
-"""Exhaustive CPU checks of the fp32 identities behind the int8 epilogues' arithmetic.
+"""CPU checks of the fp32 identities behind the int8 epilogues' arithmetic.
 
 The row-block and column-block int8 epilogues compute the block scale absmax / 127 as a
-product with RN(1/127) plus one fma correction, and turn a scaled moment into its code by
-adding 1.5 * 2^23 (the sum's rounding is the round-half-even of App. B's quantiser).
-Both are exact only if they agree with IEEE division and rintf on every input they can
-meet; kernel_arith.c checks every such input (no GPU involved).
+product with RN(1/127) plus one fma correction, and turn a moment into its code with one fma, the
+product with the scale's reciprocal plus 1.5 * 2^23, whose rounding is the round-half-even of
+App. B's quantiser, clamped afterwards.  kernel_arith.c compares the division with IEEE division on
+every input, and the code with the exact product rounded and clamped, on every value of the binades
+that codes come from (no GPU involved).
 """
 import os
 import shutil
