@@ -32,73 +32,70 @@ COPY_BYTES = 1 << 30           # size of the calibration copy (--copy-calibratio
 # --no-unfused --copy-calibration` (FETCH_SIZE, then WRITE_SIZE), each counter scaled by
 # COPY_BYTES / (what it reads for the calibration copy).  Valid only for the kernel
 # sources whose sha256 is recorded: after any change to them the figure is reported as null.
-# (The counters were taken on sources with sha256 677b4262...; the edits since then changed
-# only the kernels of fp32 state and the host-side choice of prefetch depth for T >= 1024,
-# and every kernel below compiles to the same device code.)
 TRAFFIC = {
     "sweep": {
-        "source_sha256": "54af42890281bf2601782e57ddc2958da3fb445485e524a10dc786cc63449554",
-        "fetch_kib_per_launch": 208083.6,     # FETCH_SIZE, mean over the 129 launches of a step
-        "write_kib_per_launch": 340903.9,     # WRITE_SIZE
+        "source_sha256": "334e719aaa8df90f7b824399617fc721ebb7db966f258a58e6c89b3a22e6e55e",
+        "fetch_kib_per_launch": 210557.3,     # FETCH_SIZE, mean over the 129 launches of a step
+        "write_kib_per_launch": 340886.8,     # WRITE_SIZE
         "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
         "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
-        "bytes_per_launch": 775223790,        # (fetch * fetch_scale + write * write_scale) KiB
+        "bytes_per_launch": 780272185,
     },
     "o_proj": {
-        "source_sha256": "54af42890281bf2601782e57ddc2958da3fb445485e524a10dc786cc63449554",
-        "fetch_kib_per_launch": 61657.5,     # one launch (4096 x 4096)
-        "write_kib_per_launch": 98401.0,
-        "fetch_scale": 1.99993,
-        "write_scale": 1.0,
-        "bytes_per_launch": 227032473,
+        "source_sha256": "334e719aaa8df90f7b824399617fc721ebb7db966f258a58e6c89b3a22e6e55e",
+        "fetch_kib_per_launch": 61605.2,     # one launch (4096 x 4096)
+        "write_kib_per_launch": 98385.6,     # WRITE_SIZE
+        "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
+        "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
+        "bytes_per_launch": 226909257,
     },
     "mlp": {
-        "source_sha256": "54af42890281bf2601782e57ddc2958da3fb445485e524a10dc786cc63449554",
-        "fetch_kib_per_launch": 211172.7,     # mean over the 3 launches (gate, up, down)
-        "write_kib_per_launch": 344073.3,
-        "fetch_scale": 1.99993,
-        "write_scale": 1.0,
-        "bytes_per_launch": 784796715,
+        "source_sha256": "334e719aaa8df90f7b824399617fc721ebb7db966f258a58e6c89b3a22e6e55e",
+        "fetch_kib_per_launch": 211351.4,     # mean over the 3 launches (gate, up, down)
+        "write_kib_per_launch": 344072.7,     # WRITE_SIZE
+        "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
+        "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
+        "bytes_per_launch": 785160798,
     },
     "mlp_i8": {
-        "source_sha256": "54af42890281bf2601782e57ddc2958da3fb445485e524a10dc786cc63449554",
-        "fetch_kib_per_launch": 153124.5,     # mean over the 3 launches (gate, up, down)
-        "write_kib_per_launch": 261589.0,
-        "fetch_scale": 1.99992,
-        "write_scale": 1.0,
-        "bytes_per_launch": 581454198,
+        "source_sha256": "334e719aaa8df90f7b824399617fc721ebb7db966f258a58e6c89b3a22e6e55e",
+        "fetch_kib_per_launch": 196396.8,     # mean over the 3 launches (gate, up, down)
+        "write_kib_per_launch": 231168.1,     # WRITE_SIZE
+        "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
+        "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
+        "bytes_per_launch": 638920692,
     },
     "mlp_i8r64": {
-        "source_sha256": "54af42890281bf2601782e57ddc2958da3fb445485e524a10dc786cc63449554",
-        "fetch_kib_per_launch": 155839.9,     # mean over the 3 launches (gate, up, down)
-        "write_kib_per_launch": 241004.1,
-        "fetch_scale": 1.99993,
-        "write_scale": 1.0,
-        "bytes_per_launch": 565936401,
+        "source_sha256": "334e719aaa8df90f7b824399617fc721ebb7db966f258a58e6c89b3a22e6e55e",
+        "fetch_kib_per_launch": 157705.2,     # mean over the 3 launches (gate, up, down)
+        "write_kib_per_launch": 237987.6,     # WRITE_SIZE
+        "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
+        "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
+        "bytes_per_launch": 566666633,
     },
     "mlp_fp8": {
-        "source_sha256": "54af42890281bf2601782e57ddc2958da3fb445485e524a10dc786cc63449554",
-        "fetch_kib_per_launch": 147209.0,     # mean over the 3 launches (gate, up, down)
-        "write_kib_per_launch": 229400.2,
-        "fetch_scale": 1.99992,
-        "write_scale": 1.0,
-        "bytes_per_launch": 536378457,
+        "source_sha256": "334e719aaa8df90f7b824399617fc721ebb7db966f258a58e6c89b3a22e6e55e",
+        "fetch_kib_per_launch": 152504.2,     # mean over the 3 launches (gate, up, down)
+        "write_kib_per_launch": 229379.4,     # WRITE_SIZE
+        "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
+        "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
+        "bytes_per_launch": 547200614,
     },
     "mlp_wfp8": {
-        "source_sha256": "54af42890281bf2601782e57ddc2958da3fb445485e524a10dc786cc63449554",
-        "fetch_kib_per_launch": 177867.1,     # mean over the 3 launches (gate, up, down)
-        "write_kib_per_launch": 286732.6,
-        "fetch_scale": 1.99992,
-        "write_scale": 1.0,
-        "bytes_per_launch": 657871851,
+        "source_sha256": "334e719aaa8df90f7b824399617fc721ebb7db966f258a58e6c89b3a22e6e55e",
+        "fetch_kib_per_launch": 181559.9,     # mean over the 3 launches (gate, up, down)
+        "write_kib_per_launch": 286738.4,     # WRITE_SIZE
+        "fetch_scale": 1.99993,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
+        "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
+        "bytes_per_launch": 665441783,
     },
     "mlp_wfp8_fp8": {
-        "source_sha256": "54af42890281bf2601782e57ddc2958da3fb445485e524a10dc786cc63449554",
-        "fetch_kib_per_launch": 116193.0,     # mean over the 3 launches (gate, up, down)
-        "write_kib_per_launch": 172065.1,
-        "fetch_scale": 1.99992,
-        "write_scale": 1.0,
-        "bytes_per_launch": 414148815,
+        "source_sha256": "334e719aaa8df90f7b824399617fc721ebb7db966f258a58e6c89b3a22e6e55e",
+        "fetch_kib_per_launch": 123614.1,     # mean over the 3 launches (gate, up, down)
+        "write_kib_per_launch": 172037.6,     # WRITE_SIZE
+        "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
+        "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
+        "bytes_per_launch": 429318053,
     },
 }
 

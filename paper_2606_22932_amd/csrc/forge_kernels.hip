@@ -106,7 +106,6 @@ struct Mainloop {
     static constexpr int DPC = NINST / 4;                // per math wave
     static constexpr int STAGE_BYTES = (XCH + YCH) * 16;
     static constexpr int LDS_BYTES = NS * STAGE_BYTES;
-    static_assert(2 * 20 * (XROWB > YROWB ? XROWB : YROWB) + 3 * STAGE_BYTES < 65536 || true, "");
 
     f32x16_t acc[2][2];                                  // [q sub-tile][p sub-tile]
     uint32_t voff[DPC];                                  // buffer byte offsets of this lane's DMA pieces
@@ -679,9 +678,6 @@ struct EpiRule {
     }
 };
 
-template <int BP, int BQ, int MK>
-using EpiAdamW = EpiRule<BP, BQ, MK, EPI_ADAMW>;
-
 // The absmax reductions below run on the bit patterns of non-negative floats (+0 and up),
 // whose signed-integer order is their numeric order.
 //
@@ -744,7 +740,7 @@ __device__ __forceinline__ float div127(float x)
 // exactly the 8 consecutive lanes that hold its row's 64 columns in one pass, so the new
 // block absmax closes with three DPP exchanges and each row is dequantised, updated and
 // re-quantised in a single pass: s = absmax / 127 (fp32, correctly rounded),
-// q = round_half_even(x * RN(1/s)) (the fp32 reciprocal of the scale, not a division)
+// q = round_half_even(x * RN(1/s)) of the exact product (the fp32 reciprocal, not a division)
 // clamped to [-127, 127], v codes at least 1 in a non-zero block.
 // The weight update reads the unquantised fp32 m', v'.
 template <int BP, int BQ, int NTH = NROLE>
@@ -916,11 +912,11 @@ struct Fp8 {
 // update reads the decoded state and runs in fp32 as everywhere else.
 //
 // Bound by the stream waves' instructions: with few bytes per element the epilogue (10.6 of a
-// tile's 20.9 us at T = 512) and the token loop run one after the other in a workgroup.
-// Branch-free buffer loads, codes converted in pairs, scales folded into the recurrence's
-// constants, one median per clamp and maxima recorded once per workgroup take the fp8
-// weight + moment step on 14336 x 4096 at T = 512 from 136 to 126 us, on 4096 x 4096 from
-// 45.2 to 39.8 us (fp8 moments 140 to 137 us and, on 4096 x 14336, 147 to 137 us).
+// tile's 20.9 us at T = 512) and the token loop run one after the other in a workgroup of the
+// 128 x 128 kernel.  There, branch-free buffer loads, codes converted in pairs, the scales of W and m
+// folded into the recurrence's constants, one median per clamp and maxima recorded once per
+// workgroup take the fp8 weight + moment step on 14336 x 4096 at T = 512 from 141 to 127 us (in
+// wide_kernel 122), on 4096 x 4096 from 48 to 42 us.
 template <int BP, int BQ, bool WF8, bool MF8, int NTH = NROLE>
 struct EpiQ {
     using M = EpiMap<BP, BQ, NTH>;
@@ -1423,10 +1419,11 @@ __global__ void __launch_bounds__(NT, 4) fused_kernel(GroupArgs g)
 // instructions 0.42 ms).  A 128 x 256 tile moves 12 KB for as many.  One workgroup of four
 // waves (64 rows x 128 columns each) owns a tile, two are resident per CU, one wave of each
 // on every SIMD, and every wave runs the epilogue of its own part: while one workgroup streams
-// state, the other's products run.  Measured against the 128 x 128 kernel (bf16 state,
-// AdamW): 28672 x 4096 at T = 4096 978 against 1260 us, 14336 x 4096 502 against 650 us, at
-// T = 2048 298 against 327 us, at T = 512 the same.  256 x 256 tiles (one workgroup of eight
-// waves per CU) are 1-5 % slower except on the longest loops: nothing covers their epilogue.
+// state, the other's products run.  Measured against the 128 x 128 kernel (bf16 state, AdamW, cold
+// operands): 28672 x 4096 at T = 4096 1007 against 1200 us, T = 2048 596 : 653, T = 512 304 : 277;
+// 14336 x 4096 480 : 574, 287 : 314 and 163 : 147; wide_pays() has the rule.  256 x 256 tiles (one
+// workgroup of eight waves per CU) were 1-5 % slower except on the longest loops: nothing covers
+// their epilogue.
 //
 // Token loop: a ring of three 24 KB stages (32 tokens).  The fragments of a 16-token step are
 // read from LDS while the matrix instructions of the step before run, across chunks too; one
@@ -2142,8 +2139,10 @@ __global__ void __launch_bounds__(NT_I8P, NT_I8P / 256) pipelined_i8_kernel(Grou
 // m' and sqrt(v') of the tile before any is quantised, and those are twice what the registers
 // hold, so two passes compute them from the same numbers, G (kept in the accumulators), the
 // codes and the old scales: the first updates W and takes the absmax, the second quantises.
-// The second reads the codes again, from the caches they came through a few microseconds
-// before.  Bit-identical to pipelined_i8_kernel.
+// The second reads the codes again, and not from the L2: the 64 resident tiles of an XCD have
+// 4 MB of them, as much as it holds.  The counters show both reads (MLP projections, T = 512: 402 MB
+// fetched per launch, 256 MB read once and 117 MB of codes; the memory-side cache may serve
+// the second).  Bit-identical to pipelined_i8_kernel.
 struct WideI8 {
     using M = EpiMap<32, BQ_WI8, 64>;
     static constexpr int AH = 4;                         // passes in flight
@@ -2536,10 +2535,10 @@ static int raster_rows_i8(int T)
 
 // Whether a launch of `tiles` 256 x 128 tiles with T tokens runs in wide_i8_kernel: where they
 // occupy at least three quarters of its 2 * CUs workgroups, or half with long token loops.
-// Against pipelined_i8_kernel, microseconds: 14336 x 4096 151 : 175 at T = 512, 298 : 411 at
-// T = 2048; 4096 x 4096 (512 tiles) 36 : 42 at T = 128, 46 : 57 at T = 512; 5000 x 3000 (480)
-// 52 : 64; but 4096 x 2048 (256) 32 : 31 at T = 512 and 57 : 65 at T = 2048, 2048 x 2048 (128)
-// 29 : 19.
+// Against pipelined_i8_kernel, microseconds, cold operands: 14336 x 4096 149 : 176 at T = 512,
+// 287-301 : 394 at T = 2048; 4096 x 4096 (512 tiles) 35 : 41 at T = 128, 47 : 54 at T = 512; 3000 x 5000
+// (480) 51 : 61; but 2048 x 4096 (256) 30.8 : 29.2 at T = 512, 38.8 : 38.7 at T = 1024 and 55 : 59 at
+// T = 2048, 2048 x 2048 (128) 27 : 17.
 static bool wide_i8_pays(int64_t T, int64_t tiles)
 {
     const int slots = 2 * device_cu_count();
