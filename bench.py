@@ -34,68 +34,68 @@ COPY_BYTES = 1 << 30           # size of the calibration copy (--copy-calibratio
 # sources whose sha256 is recorded: after any change to them the figure is reported as null.
 TRAFFIC = {
     "sweep": {
-        "source_sha256": "334e719aaa8df90f7b824399617fc721ebb7db966f258a58e6c89b3a22e6e55e",
-        "fetch_kib_per_launch": 210557.3,     # FETCH_SIZE, mean over the 129 launches of a step
-        "write_kib_per_launch": 340886.8,     # WRITE_SIZE
+        "source_sha256": "50cf9a1b9d6d894521e291364b216e310412b777e1120711cf7d7001757733d5",
+        "fetch_kib_per_launch": 210193.3,     # FETCH_SIZE, mean over the 129 launches of a step
+        "write_kib_per_launch": 340890.3,     # WRITE_SIZE
         "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
         "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
-        "bytes_per_launch": 780272185,
+        "bytes_per_launch": 779530327,
     },
     "o_proj": {
-        "source_sha256": "334e719aaa8df90f7b824399617fc721ebb7db966f258a58e6c89b3a22e6e55e",
-        "fetch_kib_per_launch": 61605.2,     # one launch (4096 x 4096)
-        "write_kib_per_launch": 98385.6,     # WRITE_SIZE
+        "source_sha256": "50cf9a1b9d6d894521e291364b216e310412b777e1120711cf7d7001757733d5",
+        "fetch_kib_per_launch": 62096.1,     # one launch (4096 x 4096)
+        "write_kib_per_launch": 98328.1,     # WRITE_SIZE
         "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
         "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
-        "bytes_per_launch": 226909257,
+        "bytes_per_launch": 227855700,
     },
     "mlp": {
-        "source_sha256": "334e719aaa8df90f7b824399617fc721ebb7db966f258a58e6c89b3a22e6e55e",
-        "fetch_kib_per_launch": 211351.4,     # mean over the 3 launches (gate, up, down)
-        "write_kib_per_launch": 344072.7,     # WRITE_SIZE
+        "source_sha256": "50cf9a1b9d6d894521e291364b216e310412b777e1120711cf7d7001757733d5",
+        "fetch_kib_per_launch": 210783.2,     # mean over the 3 launches (gate, up, down)
+        "write_kib_per_launch": 344072.3,     # WRITE_SIZE
         "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
         "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
-        "bytes_per_launch": 785160798,
+        "bytes_per_launch": 783996761,
     },
     "mlp_i8": {
-        "source_sha256": "334e719aaa8df90f7b824399617fc721ebb7db966f258a58e6c89b3a22e6e55e",
-        "fetch_kib_per_launch": 196396.8,     # mean over the 3 launches (gate, up, down)
-        "write_kib_per_launch": 231168.1,     # WRITE_SIZE
+        "source_sha256": "50cf9a1b9d6d894521e291364b216e310412b777e1120711cf7d7001757733d5",
+        "fetch_kib_per_launch": 196501.1,     # mean over the 3 launches (gate, up, down)
+        "write_kib_per_launch": 231168.0,     # WRITE_SIZE
         "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
         "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
-        "bytes_per_launch": 638920692,
+        "bytes_per_launch": 639134187,
     },
     "mlp_i8r64": {
-        "source_sha256": "334e719aaa8df90f7b824399617fc721ebb7db966f258a58e6c89b3a22e6e55e",
-        "fetch_kib_per_launch": 157705.2,     # mean over the 3 launches (gate, up, down)
-        "write_kib_per_launch": 237987.6,     # WRITE_SIZE
+        "source_sha256": "50cf9a1b9d6d894521e291364b216e310412b777e1120711cf7d7001757733d5",
+        "fetch_kib_per_launch": 157650.0,     # mean over the 3 launches (gate, up, down)
+        "write_kib_per_launch": 237875.4,     # WRITE_SIZE
         "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
         "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
-        "bytes_per_launch": 566666633,
+        "bytes_per_launch": 566438695,
     },
     "mlp_fp8": {
-        "source_sha256": "334e719aaa8df90f7b824399617fc721ebb7db966f258a58e6c89b3a22e6e55e",
-        "fetch_kib_per_launch": 152504.2,     # mean over the 3 launches (gate, up, down)
-        "write_kib_per_launch": 229379.4,     # WRITE_SIZE
+        "source_sha256": "50cf9a1b9d6d894521e291364b216e310412b777e1120711cf7d7001757733d5",
+        "fetch_kib_per_launch": 152503.7,     # mean over the 3 launches (gate, up, down)
+        "write_kib_per_launch": 229380.8,     # WRITE_SIZE
         "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
         "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
-        "bytes_per_launch": 547200614,
+        "bytes_per_launch": 547201024,
     },
     "mlp_wfp8": {
-        "source_sha256": "334e719aaa8df90f7b824399617fc721ebb7db966f258a58e6c89b3a22e6e55e",
-        "fetch_kib_per_launch": 181559.9,     # mean over the 3 launches (gate, up, down)
-        "write_kib_per_launch": 286738.4,     # WRITE_SIZE
-        "fetch_scale": 1.99993,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
-        "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
-        "bytes_per_launch": 665441783,
-    },
-    "mlp_wfp8_fp8": {
-        "source_sha256": "334e719aaa8df90f7b824399617fc721ebb7db966f258a58e6c89b3a22e6e55e",
-        "fetch_kib_per_launch": 123614.1,     # mean over the 3 launches (gate, up, down)
-        "write_kib_per_launch": 172037.6,     # WRITE_SIZE
+        "source_sha256": "50cf9a1b9d6d894521e291364b216e310412b777e1120711cf7d7001757733d5",
+        "fetch_kib_per_launch": 181541.4,     # mean over the 3 launches (gate, up, down)
+        "write_kib_per_launch": 286742.5,     # WRITE_SIZE
         "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
         "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
-        "bytes_per_launch": 429318053,
+        "bytes_per_launch": 665406235,
+    },
+    "mlp_wfp8_fp8": {
+        "source_sha256": "50cf9a1b9d6d894521e291364b216e310412b777e1120711cf7d7001757733d5",
+        "fetch_kib_per_launch": 123639.6,     # mean over the 3 launches (gate, up, down)
+        "write_kib_per_launch": 172035.9,     # WRITE_SIZE
+        "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
+        "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
+        "bytes_per_launch": 429368534,
     },
 }
 

@@ -277,10 +277,10 @@ struct Mainloop {
     // last ones in the loop cut a chunk's code in pieces and hold the refill back behind all of
     // its products; the chunks that refill a stage therefore have a loop of their own.
     // Microseconds, tests in every chunk against this: 1024 wide, 512 high, T = 2048 bf16 state
-    // 24.9 : 21.5, int8 columns 34.2 : 30.5; 2048 x 2048 28.7 : 27.2 and 36.7 : 32.5.  Where the
-    // launch asks for it (MAY_TEST and !steady: two workgroups of long loops on a CU, which share
-    // its operand DMA; launch_group) and with less than two rings of chunks, whose time is the
-    // fetch of the code, the loop keeps the tests.
+    // 24.9 : 21.5, int8 columns 34.2 : 30.5; 2048 x 2048 28.7 : 27.2 and 36.7 : 32.5; 256 x 256,
+    // T = 200 8.47 : 8.15.  Where the launch asks for it (MAY_TEST and !steady: two workgroups on a
+    // CU, which share its operand DMA; launch_group) and with few chunks, whose time is the fetch of
+    // the code (fp32 state 256 x 256, T = 128 10.9 : 11.2), the loop keeps the tests.
     template <bool MAY_TEST>
     __device__ __forceinline__ void body(const Args &a, unsigned char *lds, int wave, bool steady)
     {
@@ -288,7 +288,7 @@ struct Mainloop {
         uint32_t lds_base = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)lds;
         asm volatile("" : "+s"(lds_base));   // not again for every chunk, with the test for null
         auto refill = [&](int c) { issue(a, lds + ((c + NS - 1) % NS) * STAGE_BYTES, c + NS - 1, wave); };
-        if (MAY_TEST && (!steady || nch < 2 * NS)) {
+        if (MAY_TEST && (!steady || nch < NS + 2)) {
             for (int c = 0; c < nch; ++c) {
                 const bool more = c + NS - 1 < nch;
                 if (__builtin_expect(more, 1)) wait_chunk(NS - 2);
@@ -2487,7 +2487,8 @@ static hipError_t launch_group(const Args *a, int n, hipStream_t st)
     // later, behind the tests, get through it faster.  bf16 AdamW, microseconds: 4096 wide, 2048
     // high, T = 4096 73.0 against 75.6, 6144 high, T = 1536 107 : 113; 4096 x 4096, T = 2048
     // 89.8 : 93.6, T = 1024 60.3 : 59.1; with one workgroup per CU (2048 x 2048, T = 2048) 28.7 : 27.2.
-    if (a[0].T >= 1536 && g.start[n] > device_cu_count()) g.steady = 0;
+    // So do the shortest loops: 4096 x 4096, T = 224 43.5 : 44.4 (2048 x 2048 15.0 : 14.8).
+    if ((a[0].T >= 1536 || a[0].T <= 7 * TK128) && g.start[n] > device_cu_count()) g.steady = 0;
     // Prefetch depth by launch length (AdamW on bf16 state): a launch of at least 8 waves of
     // resident tiles, or with a long token loop (T >= 1024), loads all eight
     // row passes of a tile's state during its mainloop, a shorter one six.  Measured per

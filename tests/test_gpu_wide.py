@@ -169,14 +169,14 @@ def test_long_loop_group_equals_single_steps_bitwise(kind, T):
             assert torch.equal(_raw(x[k]), _raw(y[k])), k
 
 
-@pytest.mark.parametrize("T", [33, 97, 224, 2049])
+@pytest.mark.parametrize("T", [33, 97, 192, 224, 2049])
 def test_token_loop_forms_are_bitwise_neutral(T):
-    """The 128 x 128 kernel's token loop has two forms: with tests in every chunk (less than two
-    rings of chunks; T >= 2048 on more than 256 tiles, which here is the whole of 17 x 25) and
-    without (the slices of at most 8 x 25 from T = 225 on).  Fewer chunks than the ring has stages,
-    one more, a ring that goes around, and one form against the other."""
+    """The 128 x 128 kernel's token loop has two forms: with tests in every chunk (less than six
+    chunks; T <= 224 or >= 1536 on more than 256 tiles, as the whole here) and without (the slices of
+    at most 8 x 33 tiles, 200 at T = 192 and 2049).  Fewer chunks than the ring has stages, one
+    more, a ring that goes around, and one form against the other."""
     print("case", T, flush=True)
-    d_in, d_out = (D_IN, D_OUT) if T < 2048 else (3208, 2168)
+    d_in, d_out = (3208, 2168) if T in (192, 2049) else (D_IN, D_OUT)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(14)
     X, dY = _gauss((T, d_in), 1.0, gen), _gauss((T, d_out), 1e-3, gen)
