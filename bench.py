@@ -34,68 +34,68 @@ COPY_BYTES = 1 << 30           # size of the calibration copy (--copy-calibratio
 # sources whose sha256 is recorded: after any change to them the figure is reported as null.
 TRAFFIC = {
     "sweep": {
-        "source_sha256": "50cf9a1b9d6d894521e291364b216e310412b777e1120711cf7d7001757733d5",
-        "fetch_kib_per_launch": 210193.3,     # FETCH_SIZE, mean over the 129 launches of a step
-        "write_kib_per_launch": 340890.3,     # WRITE_SIZE
+        "source_sha256": "86850932dbd4df1f102bf5b360e6a74dceef40961a3098942b7d0be45e3f5957",
+        "fetch_kib_per_launch": 210439.2,     # FETCH_SIZE, mean over the 129 launches of a step
+        "write_kib_per_launch": 340885.1,     # WRITE_SIZE
         "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
         "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
-        "bytes_per_launch": 779530327,
+        "bytes_per_launch": 780028585,
     },
     "o_proj": {
-        "source_sha256": "50cf9a1b9d6d894521e291364b216e310412b777e1120711cf7d7001757733d5",
-        "fetch_kib_per_launch": 62096.1,     # one launch (4096 x 4096)
-        "write_kib_per_launch": 98328.1,     # WRITE_SIZE
+        "source_sha256": "86850932dbd4df1f102bf5b360e6a74dceef40961a3098942b7d0be45e3f5957",
+        "fetch_kib_per_launch": 61713.3,     # one launch (4096 x 4096)
+        "write_kib_per_launch": 98373.8,     # WRITE_SIZE
         "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
         "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
-        "bytes_per_launch": 227855700,
+        "bytes_per_launch": 227118554,
     },
     "mlp": {
-        "source_sha256": "50cf9a1b9d6d894521e291364b216e310412b777e1120711cf7d7001757733d5",
-        "fetch_kib_per_launch": 210783.2,     # mean over the 3 launches (gate, up, down)
-        "write_kib_per_launch": 344072.3,     # WRITE_SIZE
+        "source_sha256": "86850932dbd4df1f102bf5b360e6a74dceef40961a3098942b7d0be45e3f5957",
+        "fetch_kib_per_launch": 210419.4,     # mean over the 3 launches (gate, up, down)
+        "write_kib_per_launch": 344075.0,     # WRITE_SIZE
         "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
         "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
-        "bytes_per_launch": 783996761,
+        "bytes_per_launch": 783254494,
     },
     "mlp_i8": {
-        "source_sha256": "50cf9a1b9d6d894521e291364b216e310412b777e1120711cf7d7001757733d5",
-        "fetch_kib_per_launch": 196501.1,     # mean over the 3 launches (gate, up, down)
+        "source_sha256": "86850932dbd4df1f102bf5b360e6a74dceef40961a3098942b7d0be45e3f5957",
+        "fetch_kib_per_launch": 195485.8,     # mean over the 3 launches (gate, up, down)
         "write_kib_per_launch": 231168.0,     # WRITE_SIZE
         "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
         "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
-        "bytes_per_launch": 639134187,
+        "bytes_per_launch": 637054936,
     },
     "mlp_i8r64": {
-        "source_sha256": "50cf9a1b9d6d894521e291364b216e310412b777e1120711cf7d7001757733d5",
-        "fetch_kib_per_launch": 157650.0,     # mean over the 3 launches (gate, up, down)
-        "write_kib_per_launch": 237875.4,     # WRITE_SIZE
+        "source_sha256": "86850932dbd4df1f102bf5b360e6a74dceef40961a3098942b7d0be45e3f5957",
+        "fetch_kib_per_launch": 157565.1,     # mean over the 3 launches (gate, up, down)
+        "write_kib_per_launch": 238001.8,     # WRITE_SIZE
         "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
         "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
-        "bytes_per_launch": 566438695,
+        "bytes_per_launch": 566394260,
     },
     "mlp_fp8": {
-        "source_sha256": "50cf9a1b9d6d894521e291364b216e310412b777e1120711cf7d7001757733d5",
-        "fetch_kib_per_launch": 152503.7,     # mean over the 3 launches (gate, up, down)
-        "write_kib_per_launch": 229380.8,     # WRITE_SIZE
+        "source_sha256": "86850932dbd4df1f102bf5b360e6a74dceef40961a3098942b7d0be45e3f5957",
+        "fetch_kib_per_launch": 152439.7,     # mean over the 3 launches (gate, up, down)
+        "write_kib_per_launch": 229379.9,     # WRITE_SIZE
         "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
         "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
-        "bytes_per_launch": 547201024,
+        "bytes_per_launch": 547069035,
     },
     "mlp_wfp8": {
-        "source_sha256": "50cf9a1b9d6d894521e291364b216e310412b777e1120711cf7d7001757733d5",
-        "fetch_kib_per_launch": 181541.4,     # mean over the 3 launches (gate, up, down)
-        "write_kib_per_launch": 286742.5,     # WRITE_SIZE
+        "source_sha256": "86850932dbd4df1f102bf5b360e6a74dceef40961a3098942b7d0be45e3f5957",
+        "fetch_kib_per_launch": 181540.1,     # mean over the 3 launches (gate, up, down)
+        "write_kib_per_launch": 286746.9,     # WRITE_SIZE
         "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
         "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
-        "bytes_per_launch": 665406235,
+        "bytes_per_launch": 665408079,
     },
     "mlp_wfp8_fp8": {
-        "source_sha256": "50cf9a1b9d6d894521e291364b216e310412b777e1120711cf7d7001757733d5",
-        "fetch_kib_per_launch": 123639.6,     # mean over the 3 launches (gate, up, down)
-        "write_kib_per_launch": 172035.9,     # WRITE_SIZE
+        "source_sha256": "86850932dbd4df1f102bf5b360e6a74dceef40961a3098942b7d0be45e3f5957",
+        "fetch_kib_per_launch": 123564.1,     # mean over the 3 launches (gate, up, down)
+        "write_kib_per_launch": 172039.0,     # WRITE_SIZE
         "fetch_scale": 1.99992,               # 1 GiB copy: FETCH_SIZE reads about 524300 KiB
         "write_scale": 1.0,                   # 1 GiB copy: WRITE_SIZE reads 1048576 KiB
-        "bytes_per_launch": 429368534,
+        "bytes_per_launch": 429217090,
     },
 }
 

@@ -2447,7 +2447,8 @@ static bool wide_pays(int mk, int epi, int64_t T, int64_t tiles, bool tall)
 // - Widths that are multiples of 4096, whose rows all begin on the same memory channels: 1.00-1.07
 //   on taller matrices (8192 x 8192 1.01-1.16), but less where the matrix is wider than tall (4096
 //   wide, 2048 high 0.77-0.90; 8192 x 4096 0.92-0.97) or the runs of every other XCD begin in the
-//   middle of a group (4096 wide, 6144 high 0.88-0.92).
+//   middle of a group (4096 wide, T = 64 to 900: 6144 high 0.81-0.99, 10240 high 0.90-0.99,
+//   14336 high 0.92-1.05).
 // - 4096 wide and 25 to 33 tile rows high: all rows in one group, so that the XCDs begin on
 //   different columns: 0.99-1.07 from 25 to 31 and at 33, 1.07-1.36 at 32; at 34 and more groups
 //   of 4 are better, 3968 and 4224 wide it is 0.97-1.00.
